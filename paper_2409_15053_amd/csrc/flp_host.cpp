@@ -616,6 +616,14 @@ int filter_apply_impl(const flp_filter *p, const flp_csr *A, const double *V, in
     const int n = A->n;
     const bool fp32 = prec == FLP_PREC_FP32_FILTER;
     const size_t es = fp32 ? sizeof(float) : sizeof(double);
+    if (small_filter_fits(p, n, A->nnz, fp32) && !filter_shape_forced()) {
+        const float *a32 = nullptr;
+        if (fp32) CKR(ensure_val32(A, w.val32, &w.val32_src, &w.val32_nnz, &a32, s));
+        const flp_csr *fA = A;
+        bool sell = false;
+        CKR(workspace_storage(A, a32, fp32, format, s, &fA, &a32, &sell));
+        return launch_small_filter(p, fA, a32, sell, r, V, ldv, W, ldw, fp32, s);
+    }
     for (auto &u : w.U) CK(ensure(u, es * (size_t)n * r));
     void *U[3] = {w.U[0].p, w.U[1].p, w.U[2].p};
     const float *v32 = nullptr;

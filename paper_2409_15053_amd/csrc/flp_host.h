@@ -180,6 +180,15 @@ std::vector<ClenshawStep> clenshaw_plan(const flp_filter *p, int r, const void *
 int launch_plan_step(const flp_csr *A, const float *val32, int r, const ClenshawStep &st, bool fp32,
                      hipStream_t s, StepShape sh = StepShape{}, bool sell = false);
 
+// The whole filter of a small matrix as one launch, one workgroup per column
+// (flp_small.hip): W = p(Ahat) V with the bits of the planned launches.  A
+// (val32: its FP32 values) in CSR or, with sell, as its sliced ELL copy; V
+// and W in FP64 in both precisions.
+constexpr int kSmallMaxDegree = 384;  // its coefficients travel as kernel arguments
+bool small_filter_fits(const flp_filter *p, int n, int64_t nnz, bool fp32);
+int launch_small_filter(const flp_filter *p, const flp_csr *A, const float *val32, bool sell, int r, const double *V,
+                        int ldv, double *W, int ldw, bool fp32, hipStream_t s);
+
 // ---------------------------------------------------------------- autotuner
 struct FilterTune {
     int gw = 0;           // columns per filter launch (column-group width)
@@ -205,6 +214,7 @@ void set_autotune(int mode);
 int autotune_mode();
 // chunk: sh.chunk is forced too (else only the shape and width)
 void force_filter_shape(StepShape sh, int gw, bool chunk);
+bool filter_shape_forced();
 
 // W = p(Ahat) V (V, W n x r with leading dimensions) through the
 // workspace's Clenshaw buffers.

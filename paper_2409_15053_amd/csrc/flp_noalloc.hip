@@ -70,6 +70,9 @@ extern "C" int flp_filter_apply_noalloc(const flp_filter *p, const flp_csr *A, c
         return fail(FLP_E_NOMEM, "n * r exceeds the allocation-free limit of 1048576 elements");
     try {
         hipStream_t s = (hipStream_t)stream;
+        // a small matrix needs no scratch at all
+        if (small_filter_fits(p, A->n, A->nnz, fp32))
+            return launch_small_filter(p, A, A->val32, false, r, V, (int)ldv, W, (int)ldw, fp32, s);
         void *base = nullptr;
         CKR(scratch_ptr(&base));
         const size_t es = fp32 ? sizeof(float) : sizeof(double);

@@ -875,8 +875,14 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
     void *U[3] = {S.U[0], S.U[1], S.U[2]};
     const flp_csr *fA = S.sell ? &S.SA : A;  // the filter's copy of A
     const float *fv32 = S.sell ? S.sval32 : S.val32;
-    CKR(tune_filter(fA, fv32, S.r, fp32, true, U, fp32 ? (const void *)S.V32 : (const void *)S.Vin, S.r, S.s, &tn,
-                    S.sell));
+    // a small matrix is filtered in one launch per block step (nothing to tune or to pace)
+    const bool small = !S.unfiltered && small_filter_fits(S.filt.get(), S.n, A->nnz, fp32) && !filter_shape_forced();
+    if (small) {
+        tn.gw = S.r;
+    } else {
+        CKR(tune_filter(fA, fv32, S.r, fp32, true, U, fp32 ? (const void *)S.V32 : (const void *)S.Vin, S.r, S.s,
+                        &tn, S.sell));
+    }
     const int gw = tn.gw;
     {
         const StepShape used = step_shape_ok(gw, fp32, tn.sh) ? tn.sh : default_step_shape(gw, fp32);
@@ -930,7 +936,9 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
             }
             return FLP_OK;
         };
-        if (gw == S.r) {
+        if (small) {
+            CKR(launch_small_filter(S.filt.get(), fA, fv32, S.sell, S.r, S.Vin, S.r, S.W, S.r, fp32, S.s));
+        } else if (gw == S.r) {
             for (const auto &st : S.plan) {
                 CKR(launch_plan_step(fA, fv32, S.r, st, fp32, S.s, tn.sh, S.sell));
                 CKR(after_launch());

@@ -163,6 +163,11 @@ void force_filter_shape(StepShape sh, int gw, bool chunk) {
     g_force_chunk = chunk;
 }
 
+bool filter_shape_forced() {
+    std::lock_guard<std::mutex> lk(g_mu);
+    return g_force_shape.lpr > 0 || g_force_gw > 0 || g_force_chunk;
+}
+
 int lookup_filter_tune(const flp_csr *A, int r, bool fp32, FilterTune *out) {
     FilterTune def;
     def.gw = r;
