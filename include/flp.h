@@ -147,8 +147,9 @@ typedef struct flp_stats {
     double t_rr;           /* seconds: Rayleigh-Ritz, residuals, polish */
     double t_total;        /* seconds: whole call */
     double filter_bytes;   /* algorithmic bytes moved by the filter SpMMs */
-    double orth_bytes;     /* algorithmic bytes of the reorthogonalisation: the basis
-                              (n x k doubles) read twice per Gram-Schmidt pass */
+    double orth_bytes;     /* algorithmic bytes of the reorthogonalisation: the columns of
+                              each Gram-Schmidt pass (the last two blocks, then the whole
+                              basis of n x k doubles) read twice */
     int32_t filter_format; /* storage the filter read A in: FLP_FORMAT_CSR or FLP_FORMAT_SELL */
     int32_t filter_group_width;     /* filter launch configuration of a single solve (0 in
                                        batched and serving results): columns per launch, */
@@ -447,7 +448,7 @@ typedef struct flp_batch_stats {
     double filter_bytes;      /* algorithmic bytes of the segmented filter launches */
     double t_orth;            /* seconds: the segmented Gram-Schmidt and block QR launches
                                  (part of t_orth_check) */
-    double orth_bytes;        /* algorithmic bytes of those launches (basis read twice per pass) */
+    double orth_bytes;        /* algorithmic bytes of those launches (flp_stats.orth_bytes) */
     /* serving only (0 in batched results): */
     int32_t peak_active;      /* most requests in the active set at once */
     int32_t admission_waits;  /* times the next queued request waited for device memory */

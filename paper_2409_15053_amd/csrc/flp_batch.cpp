@@ -224,16 +224,6 @@ int ensure_pinned(void **p, size_t *have, size_t bytes) {
     return FLP_OK;
 }
 
-// Row chunk for the partial sums of a K-column projection: 512 rows (one
-// basis column per thread walks them on FMA; four waves take 32 rows per
-// MFMA step), doubled while the partial sums of one solve exceed 4M
-// doubles.
-int orth_chunk_rows(int n, int K, int c) {
-    int rows = 512;
-    while ((size_t)((n + rows - 1) / rows) * K * c > ((size_t)4 << 20)) rows *= 2;
-    return rows;
-}
-
 }  // namespace
 
 // Full reorthogonalisation and block QR of every active solve (Section
@@ -251,44 +241,34 @@ int Engine::block_step(double filter_secs) {
     CK(ensure_grow(oout, sizeof(double) * slot * ns));
     // room in each basis for this step's projection and the next block
     for (Job *j : active) CKR(ensure_basis(*j->S, (int64_t)(j->S->steps + 2) * c));
+    // each solve takes blocks by its share of the basis entries
+    double work = 0.0;
+    int64_t rows = 0;
+    int kmax = 0;
+    for (int i = 0; i < ns; ++i) {
+        orth_seg(*active[i]->S, otab_host[i]);
+        work += (double)otab_host[i].n * otab_host[i].k;
+        rows += otab_host[i].n;
+        kmax = std::max(kmax, otab_host[i].k);
+    }
+    const int mt = orth_row_tiles(rows, kmax, c);
     for (int i = 0; i < ns; ++i) {
         Solve &S = *active[i]->S;
         OrthSeg &e = otab_host[i];
-        const int n = S.n, k = (S.steps + 1) * c;
-        e.n = n;
-        e.k = k;
-        e.qcap = (int)(S.qpanels << kPanelLog2);
-        e.chunk_rows = orth_chunk_rows(n, k, c);
-        e.nchunks = (n + e.chunk_rows - 1) / e.chunk_rows;
-        e.gchunk_rows = orth_chunk_rows(n, c, c);
-        e.gnchunks = (n + e.gchunk_rows - 1) / e.gchunk_rows;
         int add[kOrthKinds] = {};
-        add[k > 128 ? kOrthFma : kOrthMfma] = (k > 128 ? (k + 255) / 256 : 1) * e.nchunks;
-        add[kOrthGram] = e.gnchunks;
-        add[kOrthRed] = (int)((k * (size_t)c + 63) / 64);
-        add[kOrthGred] = (int)((cc + 63) / 64);
-        add[kOrthRows] = (n + 255) / 256;
+        const int wgs = (int)std::min(1023.0, std::max(16.0, 1024.0 * (double)e.n * e.k / work));
+        orth_split(e, c, mt, ns == 1 ? 1023 : wgs, add);
         for (int t = 0; t < kOrthKinds; ++t) {
             opre_host[(size_t)t * ns + i] = blocks[t];
             blocks[t] += add[t];
         }
-        e.Q = S.Q;
-        e.W = S.W;
-        e.H = S.hdev;
-        e.G = S.gdev;
-        e.Ri = S.rdev;
-        e.R1 = S.gdev + 2 * cc;
-        e.R2 = S.gdev + 3 * cc;
         e.out = (double *)oout.p + (size_t)i * slot;
-        e.Vin = S.Vin;
-        e.V32 = S.V32;
         poff[i] = ptotal;
-        ptotal += std::max((size_t)e.nchunks * k * c, (size_t)e.gnchunks * cc);
+        ptotal += orth_part_elems(e, c);
         S.t_step0 = t0;
-        S.st.filter_bytes += filter_step_bytes(n, S.A->nnz, c, S.o.prec) * S.filt->m;
-        S.st.mv += (int64_t)c * S.filt->m;
-        S.st.orth_bytes += 4.0 * 8.0 * (double)n * k;
-        stats.orth_bytes += 4.0 * 8.0 * (double)n * k;
+        const double before = S.st.orth_bytes;
+        orth_account(S);
+        stats.orth_bytes += S.st.orth_bytes - before;
     }
     CK(ensure_grow(opart, sizeof(double) * std::max<size_t>(ptotal, 1)));
     for (int i = 0; i < ns; ++i) otab_host[i].part = (double *)opart.p + poff[i];
@@ -298,7 +278,7 @@ int Engine::block_step(double filter_secs) {
     std::memcpy(ostage + tb, opre_host.data(), pb);
     CK(ensure_grow(otab, tb + pb));
     CK(hipMemcpyAsync(otab.p, ostage, tb + pb, hipMemcpyHostToDevice, s));
-    OrthPlan plan{(const OrthSeg *)otab.p, (const int *)((const char *)otab.p + tb), ns, {}};
+    OrthPlan plan{(const OrthSeg *)otab.p, (const int *)((const char *)otab.p + tb), OrthSeg{}, ns, mt, {}};
     for (int t = 0; t < kOrthKinds; ++t) plan.blocks[t] = blocks[t];
     CK(launch_seg_orth(plan, c, s));
     CKR(ensure_pinned((void **)&oout_pin, &oout_pin_bytes, sizeof(double) * slot * ns));
@@ -312,35 +292,8 @@ int Engine::block_step(double filter_secs) {
         if (j->code != FLP_OK) continue;
         S.st.t_mv += filter_secs;
         const double *o = oout_pin + (size_t)i * slot;
-        const double status = o[2 * cc];
-        if (status == 2.0) {
-            j->code = fail(FLP_E_DEVICE, "block QR: second Cholesky pass broke down");
-            j->msg = last_error_cstr();
-            continue;
-        }
-        S.D_all.insert(S.D_all.end(), o, o + cc);
-        if (status == 1.0) {
-            // numerically dependent columns: the synchronous repair path on
-            // the projected block, then the copies the kernels skipped
-            const int k = (S.steps + 1) * c;
-            int rc = block_qr_impl(S.W, S.n, c, &S.Q, k, S.Sj, S.o.seed, 1000 + S.steps, s, nullptr);
-            if (rc == FLP_OK && k + c <= (int)(S.qpanels << kPanelLog2) &&
-                launch_copy_block(S.n, c, 1.0, S.W, c, S.Q, k, nullptr, 0, s) != hipSuccess)
-                rc = fail(FLP_E_DEVICE, "basis copy failed");
-            if (rc == FLP_OK &&
-                launch_copy_block(S.n, c, 1.0, S.W, c, plain_mat(S.Vin, c), 0, S.V32, c, s) != hipSuccess)
-                rc = fail(FLP_E_DEVICE, "input copy failed");
-            if (rc != FLP_OK) {
-                j->code = rc;
-                j->msg = last_error_cstr();
-                continue;
-            }
-        } else {
-            S.Sj.assign(o + cc, o + 2 * cc);
-        }
-        S.S_all.insert(S.S_all.end(), S.Sj.begin(), S.Sj.end());
-        ++S.steps;
-        S.st.t_orth += dt;
+        j->code = step_orth_take(S, o);
+        if (j->code != FLP_OK) j->msg = last_error_cstr();
     }
     return FLP_OK;
 }
@@ -426,7 +379,7 @@ int Engine::step() {
     CKR(block_step(ms * 1e-3));
     // convergence checks: applied when their pool task has finished, started
     // at the cadence (the solves keep stepping meanwhile)
-    run_phase([](Solve &S) { return step_check(S, true, false); });
+    run_phase([](Solve &S) { return step_check(S); });
     std::vector<Job *> keep, done;
     for (Job *j : active) {
         if (j->code == FLP_OK && !j->S->done)

@@ -44,24 +44,21 @@ __device__ __forceinline__ const double *col_base(const DMat &m, int q) {
     return m.p + (int64_t)(q >> m.lpw) * m.ps + (q & ((1 << m.lpw) - 1));
 }
 
-// C = beta C + alpha A B for one block of 4 waves: row block rblk (each wave
-// MT row tiles of 16 rows) and column block cblk (NT tiles of 16 columns).
-// The k index inside a group of 16 is permuted (k = 4 * (l/16) + step) so
-// each lane reads 4 contiguous A entries with two 16-byte loads.  A group of
-// 16 k values never straddles a panel.  Loads are unconditional: rows past n
-// and columns past c are clamped (they only feed outputs that are not
-// written) and B rows past K are zeroed.  A and C may be the same block
-// (in-place C = A B): each wave reads all of its rows of A before it writes
-// those rows of C.
-template <int MT, int NT>
-__device__ __forceinline__ void gemm_nn_rows(int n, int K, int c, double alpha, const DMat &A,
-                                             const double *__restrict__ B, int64_t ldb, double beta, double *C,
-                                             int64_t ldc, bool vec_a, int rblk, int cblk) {
-    const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
-    const int row0 = (rblk * 4 + wave) * (16 * MT);
-    if (row0 >= n) return;
+// acc = A B for the MT row tiles of 16 rows that start at row0 (row indices
+// past n - 1 are clamped: they only feed outputs the caller does not write)
+// and NT column tiles of 16 columns (tile cblk NT + j; columns past c - 1
+// clamped likewise); D layout per tile (mfma16x16x4 above).  The k index
+// inside a group of 16 is permuted (k = 4 * (l/16) + step) so each lane reads
+// 4 contiguous A entries with two 16-byte loads.  A group of 16 k values
+// never straddles a panel.  Loads are unconditional; B rows past K are
+// zeroed.  A's columns start at ka (a multiple of 16).  PIPE: the loads of
+// the next group are in flight while this group's products run.
+template <int MT, int NT, bool PIPE = false>
+__device__ __forceinline__ void gemm_nn_acc(int n, int K, int c, const DMat &A, const double *__restrict__ B,
+                                            int64_t ldb, bool vec_a, int row0, int cblk, dbl4 (&acc)[MT][NT],
+                                            int ka = 0) {
+    const int lane = threadIdx.x % WAVE;
     const int kq = lane / 16, m = lane % 16;
-    dbl4 acc[MT][NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -74,10 +71,10 @@ __device__ __forceinline__ void gemm_nn_rows(int n, int K, int c, double alpha, 
     for (int i = 0; i < MT; ++i) roff[i] = (int64_t)min(row0 + i * 16 + m, n - 1) * A.ld;
     const int kfull = vec_a ? (K & ~15) : 0;
     int k0 = 0;
-    for (; k0 < kfull; k0 += 16) {
-        const int kb = k0 + 4 * kq;  // this lane's 4 contiguous k values
-        const auto abase = as_global(col_base(A, kb));
-        double a[MT][4];
+    double a[MT][4], b[4][NT];
+    const auto load = [&](int k, double (&a)[MT][4], double (&b)[4][NT]) {
+        const int kb = k + 4 * kq;  // this lane's 4 contiguous k values
+        const auto abase = as_global(col_base(A, ka + kb));
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
             const auto ap = abase + roff[i];
@@ -88,17 +85,34 @@ __device__ __forceinline__ void gemm_nn_rows(int n, int K, int c, double alpha, 
             a[i][2] = x1.x;
             a[i][3] = x1.y;
         }
-        double b[4][NT];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int j = 0; j < NT; ++j) b[q][j] = as_global(B)[(int64_t)(kb + q) * ldb + col[j]];
+    };
+    if (PIPE && k0 < kfull) load(0, a, b);
+    for (; k0 < kfull; k0 += 16) {
+        double an[MT][4], bn[4][NT];
+        if constexpr (PIPE)
+            load(min(k0 + 16, kfull - 16), an, bn);
+        else
+            load(k0, a, b);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
                 for (int j = 0; j < NT; ++j) acc[i][j] = mfma16x16x4(a[i][q], b[q][j], acc[i][j]);
+        if constexpr (PIPE) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) a[i][q] = an[i][q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) b[q][j] = bn[q][j];
+        }
     }
     for (; k0 < K; k0 += 16) {  // ragged tail (or unaligned A): scalar loads
         const int kb = k0 + 4 * kq;
@@ -106,7 +120,7 @@ __device__ __forceinline__ void gemm_nn_rows(int n, int K, int c, double alpha, 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int kk = min(kb + q, K - 1);
-            const auto ap = as_global(col_base(A, kk));
+            const auto ap = as_global(col_base(A, ka + kk));
 #pragma unroll
             for (int i = 0; i < MT; ++i) a[i][q] = ap[roff[i]];
 #pragma unroll
@@ -122,6 +136,22 @@ __device__ __forceinline__ void gemm_nn_rows(int n, int K, int c, double alpha, 
 #pragma unroll
                 for (int j = 0; j < NT; ++j) acc[i][j] = mfma16x16x4(a[i][q], b[q][j], acc[i][j]);
     }
+}
+
+// C = beta C + alpha A B for one block of 4 waves: row block rblk (each wave
+// MT row tiles of 16 rows) and column block cblk (NT tiles of 16 columns).
+// A and C may be the same block (in-place C = A B): each wave reads all of
+// its rows of A before it writes those rows of C.
+template <int MT, int NT, bool PIPE = false>
+__device__ __forceinline__ void gemm_nn_rows(int n, int K, int c, double alpha, const DMat &A,
+                                             const double *__restrict__ B, int64_t ldb, double beta, double *C,
+                                             int64_t ldc, bool vec_a, int rblk, int cblk) {
+    const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+    const int row0 = (rblk * 4 + wave) * (16 * MT);
+    if (row0 >= n) return;
+    const int kq = lane / 16, m = lane % 16;
+    dbl4 acc[MT][NT];
+    gemm_nn_acc<MT, NT, PIPE>(n, K, c, A, B, ldb, vec_a, row0, cblk, acc);
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll

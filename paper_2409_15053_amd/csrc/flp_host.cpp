@@ -265,9 +265,16 @@ void Workspace::release_all() {
                   &W,      &Vin,    &Q,          &Y,    &AY,    &X,        &AX,       &resid_part,
                   &PU[0],  &PU[1],  &PU[2],      &PR,   &PC,    &sell_off, &sell_col, &sell_val};
     for (Buf *b : all) b->release();
+    if (pin) (void)hipHostFree(pin);
+    pin = nullptr;
+    pin_elems = 0;
     val32_src = nullptr;
     val32_nnz = 0;
     sell_valid = false;
+}
+
+Workspace::~Workspace() {
+    if (pin) (void)hipHostFree(pin);
 }
 
 namespace {
@@ -872,6 +879,21 @@ int small_dev(size_t elems, double **out) {
     return FLP_OK;
 }
 
+// The calling thread's pinned host scratch (contents live until the next use).
+int pinned_scratch(size_t elems, double **out) {
+    Workspace &w = ws();
+    if (w.pin_elems < elems) {
+        if (w.pin) CK(hipHostFree(w.pin));
+        w.pin = nullptr;
+        w.pin_elems = 0;
+        const size_t want = std::max<size_t>(elems, 2048);
+        CK(hipHostMalloc((void **)&w.pin, sizeof(double) * want, hipHostMallocDefault));
+        w.pin_elems = want;
+    }
+    *out = w.pin;
+    return FLP_OK;
+}
+
 // C (K x c, host or device) = A^T B with A n x K (lda), B n x c (ldb).
 // dev_out: device K x c row-major; host_out (optional) receives a copy
 // (synchronises the stream).
@@ -911,35 +933,46 @@ int cgs2(DMat Q, int k, int n, double *W, int r, double *hdev, hipStream_t s) {
 int block_qr_impl(double *W, int n, int r, const DMat *Q, int k, std::vector<double> &S,
                   uint64_t seed, uint64_t sid, hipStream_t s, bool *replaced, int depth) {
     if (depth > 3) return fail(FLP_E_DEVICE, "block QR: could not repair a rank-deficient block");
+    const size_t rr = (size_t)r * r;
     double *dev = nullptr;
-    CKR(small_dev((size_t)2 * std::max<int64_t>(k, r) * r + 4 * (size_t)r * r + 64, &dev));
-    double *gdev = dev, *rdev = dev + r * r, *hdev = dev + 2 * r * r;
-    std::vector<double> G((size_t)r * r), R1, R2, Ri;
-    std::vector<int> bad, bad2;
-    // pass 1
-    CKR(gram_tn(n, r, r, plain_mat(W, r), W, r, gdev, G.data(), s));
-    double fro2 = 0.0;
-    for (int i = 0; i < r; ++i) fro2 += std::max(G[i * r + i], 0.0);
-    const double thr = 1e-7 * std::sqrt(fro2);
-    cholesky_flag(r, G.data(), std::max(thr * thr, 1e-300), R1, bad);
-    int nbad = 0;
-    for (int i = 0; i < r; ++i) nbad += bad[i];
-    upper_inverse(r, R1, Ri);
-    CK(h2d(rdev, Ri.data(), sizeof(double) * r * r, s));
-    CK(launch_gemm_nn(n, r, r, 1.0, plain_mat(W, r), rdev, r, 0.0, W, r, s));
-    if (nbad == 0) {
-        // pass 2 on the (nearly) orthonormal block
-        CKR(gram_tn(n, r, r, plain_mat(W, r), W, r, gdev, G.data(), s));
-        cholesky_flag(r, G.data(), 1e-300, R2, bad2);
-        for (int i = 0; i < r; ++i)
-            if (bad2[i]) return fail(FLP_E_DEVICE, "block QR: second Cholesky pass broke down");
-        upper_inverse(r, R2, Ri);
-        CK(h2d(rdev, Ri.data(), sizeof(double) * r * r, s));
-        CK(launch_gemm_nn(n, r, r, 1.0, plain_mat(W, r), rdev, r, 0.0, W, r, s));
-        matmul_upper(r, R2, R1, S);
-        CK(hipStreamSynchronize(s));
+    CKR(small_dev((size_t)2 * std::max<int64_t>(k, r) * r + 7 * rr + 64, &dev));
+    double *gdev = dev, *rdev = dev + rr, *hdev = dev + 7 * rr + 8;
+    // both factorisations on the device (flp_seg_orth.hip): one round trip
+    OrthPlan p{};
+    p.nseg = 1;
+    p.one.n = n;
+    p.one.W = p.one.Vin = W;
+    p.one.G = gdev;
+    p.one.R1 = dev + rr;
+    p.one.Ri1 = dev + 2 * rr;
+    p.one.Ri2 = dev + 3 * rr;
+    p.one.out = dev + 4 * rr;
+    orth_split(p.one, r, 1, 1024, p.blocks);
+    Workspace &w = ws();
+    CK(ensure(w.partials, sizeof(double) * orth_part_elems(p.one, r)));
+    p.one.part = (double *)w.partials.p;
+    CK(launch_block_qr(p, r, s));
+    const size_t cnt = 6 * rr + 1;  // G, R1, the inverses, D_j (unused), S_j, status
+    double *h = nullptr;
+    CKR(pinned_scratch(cnt, &h));
+    CK(hipMemcpyAsync(h, dev, sizeof(double) * cnt, hipMemcpyDeviceToHost, s));
+    CK(hipStreamSynchronize(s));
+    const int status = (int)h[6 * rr];
+    if (status == kOrthBreakdown) return fail(FLP_E_DEVICE, "block QR: second Cholesky pass broke down");
+    if (status == kOrthOk) {
+        S.assign(h + 5 * rr, h + 6 * rr);
         return FLP_OK;
     }
+    // numerically dependent columns: W is as it came, its Gram matrix in h
+    std::vector<double> R1, Ri;
+    std::vector<int> bad;
+    double fro2 = 0.0;
+    for (int i = 0; i < r; ++i) fro2 += std::max(h[i * r + i], 0.0);
+    const double thr = 1e-7 * std::sqrt(fro2);
+    cholesky_flag(r, h, std::max(thr * thr, 1e-300), R1, bad);
+    upper_inverse(r, R1, Ri);
+    CK(h2d(rdev, Ri.data(), sizeof(double) * rr, s));
+    CK(launch_gemm_nn(n, r, r, 1.0, plain_mat(W, r), rdev, r, 0.0, W, r, s));
     // repair: the good columns of W are now orthonormal; dependent ones are
     // replaced by random vectors, the block is re-orthogonalised against Q and
     // normalised again: W_orig ~= Qn (S2 S1) with S1 = R1 minus its bad rows.

@@ -119,6 +119,12 @@ struct Workspace {
     bool sell_fp32 = false, sell_built = false, sell_valid = false;
     flp_csr sell_A{};
     const float *sell_val32 = nullptr;
+    double *pin = nullptr;  // pinned host scratch (pinned_scratch)
+    size_t pin_elems = 0;
+    Workspace() = default;
+    Workspace(const Workspace &) = delete;
+    Workspace &operator=(const Workspace &) = delete;
+    ~Workspace();
     void release_all();
 };
 Workspace &ws();
@@ -139,6 +145,7 @@ int check_symmetric(const flp_csr *A, double tol, hipStream_t s);
 int check_csr(const flp_csr *A);
 hipError_t h2d(void *dst, const void *src, size_t bytes, hipStream_t s);
 int small_dev(size_t elems, double **out);
+int pinned_scratch(size_t elems, double **out);
 
 // ---------------------------------------------------------------- filter
 double cheb_scalar(const std::vector<double> &b, double z);
@@ -349,12 +356,10 @@ struct Solve {
     flp_stats st{};
     double t_start = 0;
     int code = FLP_OK;  // first error
-    // block-step staging: pinned host h1, h2, G, R^{-1} (r x r each) and the
-    // device Gram / R^{-1} blocks behind the projection coefficients
+    // block-step outputs: pinned host copy of D_j, S_j and the status; the
+    // device r x r blocks (OrthSeg) behind the projection coefficients
     double *pin = nullptr;
-    double *gdev = nullptr, *rdev = nullptr;
-    std::vector<double> R1;
-    bool slow = false;      // this step's block needed the rank repair path
+    double *gdev = nullptr;
     int checked_step = -1;  // block step whose convergence check was started
     EigLog eig;             // rotation log of the deciding check's T_k
     std::shared_ptr<CheckTask> check;  // check in flight (its T_k may be behind the current step)
@@ -371,28 +376,29 @@ int solve_setup(Solve &S);
 // Grows the basis allocation (by doubling, on S.s, synchronous) so that it
 // holds at least cols columns (capped at max_basis).
 int ensure_basis(Solve &S, int64_t cols);
-// One block step of a single solve after the filter has produced W, in
-// phases separated by a stream synchronisation (the batched engine does the
-// first three for all its solves at once with the segmented launches of
-// Engine::block_step, then calls step_check per solve):
-//   step_orth_launch: CGS2 against the basis, Gram matrix of W (async);
-//   step_qr1:         D_j; first Cholesky factor; apply it; second Gram (async);
-//   step_qr2:         second Cholesky factor; apply it; S_j;
+// One block step after the filter has produced W (the batched engine issues
+// its solves' launches together, in Engine::block_step, and then uses the
+// last two per solve):
+//   step_orth_launch: the launches of flp_seg_orth.hip for one solve, which
+//                     write Q_{j+1} into the basis and the next filter input,
+//                     and the copy of D_j, S_j and the status (async);
+//   step_orth_take:   the host's part with that copy (out): D_j and S_j join
+//                     T_k; a flagged step is repaired (synchronous);
 //   step_check:       applies a finished convergence check; at the cadence
 //                     starts the next one on the host pool (the solve keeps
 //                     stepping meanwhile: if that check decides convergence,
 //                     the result comes from the checked T_k and the extra
-//                     steps are dropped); else the new block joins the basis
-//                     and becomes the next input.
+//                     steps are dropped).
 int step_orth_launch(Solve &S);
-int step_qr1(Solve &S);
-int step_qr2(Solve &S);
-// copy_next = false: the caller has already written the new block into the
-// basis and the next filter input
-int step_check(Solve &S, bool async = true, bool copy_next = true);
+int step_orth_take(Solve &S, const double *out);
+int step_check(Solve &S, bool async = true);
+// the solve's part of a block-step launch (all but its block split and
+// partial sums), and the statistics of the step
+void orth_seg(const Solve &S, OrthSeg &e);
+void orth_account(Solve &S);
 // waits for and applies a check in flight (no-op when there is none)
 int wait_check(Solve &S);
-// all four phases with synchronisations (single solve)
+// all three with a synchronisation (single solve)
 int solve_after_filter(Solve &S);
 // Ritz vectors, Rayleigh-Ritz with A, FP32 polish, result
 int solve_finish(Solve &S, flp_result **out);

@@ -178,41 +178,65 @@ hipError_t launch_polish_last(int n, const int32_t *rowptr, const int32_t *colin
                               const double *ptheta, hipStream_t s, bool sell = false, int chunk = 0,
                               bool win = false);
 
-// One solve's part of a segmented block step (full reorthogonalisation of
-// the filtered block W against the basis Q, then W = Q_{j+1} S_j by
-// Cholesky QR twice) with block width c <= 16; every pointer is device memory.
+// One solve's part of a block step (reorthogonalisation of the filtered
+// block W against the basis Q, then W = Q_{j+1} S_j by Cholesky QR twice)
+// with block width c <= 16; every pointer is device memory.  See
+// flp_seg_orth.hip for the stages.
 struct OrthSeg {
-    int n;                        // rows
-    int k;                        // basis columns so far (Q_1 .. Q_j)
-    int qcap;                     // basis capacity in columns
-    int chunk_rows, nchunks;      // row chunks of the projection partial sums
-    int gchunk_rows, gnchunks;    // row chunks of the Gram partial sums
-    int pad;
-    DMat Q;                       // basis (panelled)
-    double *W;                    // n x c, ld c: the filtered block
-    double *H;                    // H1 then H2, k x c each (row-major)
-    double *G;                    // c x c Gram matrix
-    double *R1, *R2, *Ri;         // c x c: first and second factor, current inverse
-    double *part;                 // partial sums: max(nchunks k, gnchunks c) c doubles
-    double *out;                  // D_j (c x c), S_j (c x c), status (0 ok, 1 dependent columns, 2 breakdown)
-    double *Vin;                  // next filter input, n x c
-    float *V32;                   // its FP32 copy (or null)
+    int n;                // rows
+    int k, kl;            // basis columns so far (Q_1 .. Q_j); the local pass covers columns kl .. k - 1
+    int qcap;             // basis capacity in columns
+    int lrows, lblk;      // rows per block and blocks of the passes over W (local projection, Gram, QR)
+    int prows, pchunks;   // row chunks of the full projection
+    int urows, ublk;      // rows per block and blocks of the updates
+    int fma, pad;         // 1: the full projection runs on FMA (tn_use_fma)
+    DMat Q;               // basis
+    double *W;            // n x c, ld c: the filtered block
+    double *H;            // local coefficients ((k - kl) x c), and the full pass's (k x c) at H + k c
+    double *G;            // c x c Gram matrix
+    double *R1, *Ri1, *Ri2;  // c x c: first factor, inverses of the first and second
+    double *part;         // partial sums (orth_part_elems)
+    double *out;          // D_j (c x c), S_j (c x c), status, unused (kOrth* below)
+    double *Vin;          // next filter input, n x c (W itself: normalised in place)
+    float *V32;           // its FP32 copy (or null)
 };
-// Launch kinds of a segmented block step: projection on FMA (solves with
-// k > 128) or MFMA (k <= 128), Gram matrix, reduction of k x c, reduction
-// of c x c, blocks of 256 rows.  A solve has no blocks in a kind it skips.
-enum { kOrthFma = 0, kOrthMfma, kOrthGram, kOrthRed, kOrthGred, kOrthRows, kOrthKinds };
-// Launch bookkeeping of one segmented block step: the device table, one
-// prefix array of first blocks per kind (nseg each, kind-major) and each
-// kind's block count.
+// status of a block step: done; numerically dependent columns; breakdown of
+// the second factor; the full pass took away more than it left (another
+// pass is needed).  1 and 3 leave the projected block in W.
+enum { kOrthOk = 0, kOrthDependent = 1, kOrthBreakdown = 2, kOrthAgain = 3 };
+// Launch kinds of a block step: blocks over W, reduction of the local
+// coefficients, updates, full projection on FMA or MFMA, reduction of the
+// full coefficients and of a Gram matrix.
+enum { kOrthLocal = 0, kOrthRedL, kOrthUpd, kOrthFma, kOrthMfma, kOrthRedH, kOrthRedG, kOrthKinds };
+// Launch bookkeeping: the device table with one prefix array of first blocks
+// per kind (nseg each, kind-major), or a single solve passed by value (tab
+// null, nseg 1); each kind's block count.
 struct OrthPlan {
     const OrthSeg *tab;
     const int *pre;
+    OrthSeg one;
     int nseg;
+    int mt;  // row tiles of the updates (orth_row_tiles of all the rows)
     int blocks[kOrthKinds];
 };
-// The 14 or 16 launches of one block step for every solve in the plan.
+// Row tiles per wave of W -= Q H for c columns of W against kmax basis
+// columns: 2, 8, or 3 for two tiles with the next group's loads in flight
+// (gemm_nn_acc's PIPE); orth_row_tiles: or 1 for a few rows.
+int nn_row_tiles(int kmax, int c);
+int orth_row_tiles(int64_t rows, int kmax, int c);
+// whether the projection of c columns on K basis columns runs on FMA
+bool tn_use_fma(int K, int c);
+// Splits the work of one solve over blocks (e.n, e.k, e.kl set; wgs: the
+// blocks its share of a launch should take) and adds its block counts.
+void orth_split(OrthSeg &e, int c, int mt, int wgs, int (&blocks)[kOrthKinds]);
+// first column of the local pass for k basis columns: the last two blocks,
+// from a multiple of 16 (a whole group of the MFMA products)
+inline int orth_local_first(int k, int c) { return (k > 2 * c ? k - 2 * c : 0) & ~15; }
+size_t orth_part_elems(const OrthSeg &e, int c);
+// The launches of one block step for every solve in the plan.
 hipError_t launch_seg_orth(const OrthPlan &p, int c, hipStream_t s);
+// Only the normalisation (the Gram matrix of W first): one.k = one.kl = 0.
+hipError_t launch_block_qr(const OrthPlan &p, int c, hipStream_t s);
 
 // Partial sums for C = A^T B over row chunks: A n x K (lda), B n x c (ldb).
 // partials[chunk][K * c] (row-major K x c).  Returns the number of chunks

@@ -37,42 +37,50 @@ __global__ __launch_bounds__(256) void gemm_tn_partial_kernel(int n, int K, int 
 }
 
 // Sum of the per-chunk partials in a fixed order (deterministic): each
-// block owns 64 outputs; its 4 thread rows split the chunks and combine
-// through LDS.  sym (a square result whose partials exist on and above the
-// diagonal only): entry (i, j) below the diagonal takes the sums of (j, i).
+// block owns 16 outputs; its 16 thread rows split the chunks, eight loads in
+// flight each, and combine through LDS (512 chunks of 2560 outputs 7 us; 64
+// outputs per block and 4 thread rows took 13).  sym (a square result whose
+// partials exist on and above the diagonal only): entry (i, j) below the
+// diagonal takes the sums of (j, i).
 __global__ __launch_bounds__(256) void reduce_partials_kernel(int nchunks, int total, int c,
                                                               const double *__restrict__ partials,
                                                               double *__restrict__ C, int ldc, bool sym) {
-    __shared__ double red[4][64];
-    const int tx = threadIdx.x % 64, ty = threadIdx.x / 64;
-    const int o = blockIdx.x * 64 + tx;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    __shared__ double red[16][17];
+    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
+    const int o = blockIdx.x * 16 + tx;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
     if (o < total) {
         const int i = o / c, j = o % c;
         const double *p = partials + ((sym && i > j) ? j * c + i : o);
         int q = ty;
-        for (; q + 12 < nchunks; q += 16) {
-            s0 += p[(size_t)q * total];
-            s1 += p[(size_t)(q + 4) * total];
-            s2 += p[(size_t)(q + 8) * total];
-            s3 += p[(size_t)(q + 12) * total];
+        for (; q + 112 < nchunks; q += 128) {
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = p[(size_t)(q + 16 * u) * total];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s[u % 4] += x[u];
         }
-        for (; q < nchunks; q += 4) s0 += p[(size_t)q * total];
+        for (; q < nchunks; q += 16) s[0] += p[(size_t)q * total];
     }
-    red[ty][tx] = (s0 + s1) + (s2 + s3);
+    red[ty][tx] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
-    if (ty == 0 && o < total) C[(size_t)(o / c) * ldc + o % c] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
+    if (ty == 0 && o < total) {
+        double t = 0.0;
+#pragma unroll
+        for (int y = 0; y < 16; ++y) t += red[y][tx];
+        C[(size_t)(o / c) * ldc + o % c] = t;
+    }
 }
 
 // C = beta C + alpha A B (see gemm_nn_rows): one block of 4 waves per
 // 4 x 16 MT rows and 16 NT columns, blocks renumbered per XCD.
-template <int MT, int NT>
+template <int MT, int NT, bool PIPE>
 __global__ __launch_bounds__(256) void gemm_nn_kernel(int n, int K, int c, double alpha, DMat A,
                                                       const double *__restrict__ B, int64_t ldb, double beta,
                                                       double *C, int64_t ldc, bool vec_a) {
     const int nct = (c + 16 * NT - 1) / (16 * NT);
     const int wg = xcd_tile(blockIdx.x, gridDim.x);
-    gemm_nn_rows<MT, NT>(n, K, c, alpha, A, B, ldb, beta, C, ldc, vec_a, wg / nct, wg % nct);
+    gemm_nn_rows<MT, NT, PIPE>(n, K, c, alpha, A, B, ldb, beta, C, ldc, vec_a, wg / nct, wg % nct);
 }
 
 }  // namespace
@@ -88,10 +96,10 @@ namespace {
 // element, far below what the FMA units sustain at HBM speed, so it needs
 // no matrix cores.
 template <int C, int UNR>
-__global__ __launch_bounds__(256) void gemm_tn_fma_kernel(int n, int K, int chunk_rows, DMat A,
+__global__ __launch_bounds__(64) void gemm_tn_fma_kernel(int n, int K, int chunk_rows, DMat A,
                                                           const double *__restrict__ B, int64_t ldb,
                                                           double *__restrict__ partials) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
+    const int q = blockIdx.x * WAVE + threadIdx.x;
     if (q >= K) return;  // no block-level synchronisation follows: idle columns leave at once
     const int chunk = blockIdx.y;
     const int r0 = chunk * chunk_rows, r1 = min(n, r0 + chunk_rows);
@@ -110,16 +118,16 @@ __global__ __launch_bounds__(256) void gemm_tn_fma_kernel(int n, int K, int chun
 // loaded element hold it back.  Measured at n = 1e6 (TB/s, FMA / MFMA):
 // c = 8: K = 128 3.5 / 5.4, 256 5.6 / 5.4, 512 6.0 / 5.5, 768 6.1 / 5.6;
 // c = 16: K = 128 2.6 / 5.5, 352 3.8 / 5.0, 768 5.0 / 5.4.
-static bool tn_use_fma(int K, int c) { return c == 8 && K >= 256; }
+bool tn_use_fma(int K, int c) { return c == 8 && K >= 256; }
 
 TnPlan plan_tn(int n, int K, int c) {
     TnPlan p;
     if (tn_use_fma(K, c)) {
-        // FMA path: about 1024 blocks of 256 columns x chunk_rows rows (about
+        // FMA path: about 4096 blocks of 64 columns x chunk_rows rows (about
         // 1000-2000 rows each at n = 1e6, the fastest chunking measured), the
         // partial buffer kept near 32M doubles at most
-        const int ncb = (K + 255) / 256;
-        int nch = std::max(1, std::min(1024, 1024 / ncb));
+        const int ncb = (K + WAVE - 1) / WAVE;
+        int nch = std::max(1, std::min(1024, 4096 / ncb));
         int rows = std::max(64, (n + nch - 1) / nch);
         rows = (rows + 63) / 64 * 64;
         while ((size_t)((n + rows - 1) / rows) * K * c > (size_t)(32u << 20)) rows *= 2;
@@ -146,8 +154,8 @@ TnPlan plan_tn(int n, int K, int c) {
 hipError_t launch_gemm_tn_partial(const TnPlan &pl, int n, int K, int c, DMat A, const double *B, int64_t ldb,
                                   double *partials, hipStream_t s, bool sym) {
     if (tn_use_fma(K, c)) {
-        dim3 grid((K + 255) / 256, pl.nchunks);
-        hipLaunchKernelGGL((gemm_tn_fma_kernel<8, 8>), grid, dim3(256), 0, s, n, K, pl.chunk_rows, A, B, ldb,
+        dim3 grid((K + WAVE - 1) / WAVE, pl.nchunks);
+        hipLaunchKernelGGL((gemm_tn_fma_kernel<8, 8>), grid, dim3(WAVE), 0, s, n, K, pl.chunk_rows, A, B, ldb,
                            partials);
         return hipGetLastError();
     }
@@ -172,37 +180,41 @@ hipError_t launch_gemm_tn_partial(const TnPlan &pl, int n, int K, int c, DMat A,
 hipError_t launch_reduce_partials(const TnPlan &pl, int K, int c, const double *partials, double *C, int ldc,
                                   hipStream_t s, bool sym) {
     int total = K * c;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((total + 63) / 64), dim3(256), 0, s, pl.nchunks, total, c,
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((total + 15) / 16), dim3(256), 0, s, pl.nchunks, total, c,
                        partials, C, ldc, sym && K == c);
     return hipGetLastError();
+}
+
+// Measured at n = 1e6 (us; two tiles / two with the next group's loads in
+// flight / eight): 8 columns, K = 96 171 / 177 / 206, K = 160 285 / 294 / 300,
+// K = 320 - / 546 / 578, K = 640 - / 1010 / 1031; 16 columns, K = 160 302 /
+// 309 / -, K = 320 - / 591 / 601, K = 720 - / 1185 / 1157; n = 27000, 8
+// columns, K = 300: 19 / 16 / -.
+int nn_row_tiles(int kmax, int c) {
+    if (kmax < 256) return 2;
+    return c <= 8 ? 3 : (kmax >= 320 ? 8 : 2);
 }
 
 hipError_t launch_gemm_nn(int n, int K, int c, double alpha, DMat A, const double *B, int64_t ldb, double beta,
                           double *C, int64_t ldc, hipStream_t s) {
     if (n <= 0 || c <= 0) return hipSuccess;
     bool vec_a = (A.ld % 2 == 0) && (A.ps % 2 == 0) && ((reinterpret_cast<uintptr_t>(A.p) & 15) == 0);
-    if (c <= 16) {
-        // row tiles per wave: 2 up to a few hundred basis columns, 8 beyond
-        // (more A loads in flight per MFMA chain); at n = 1e6 this streams
-        // Q at 5.0-5.6 TB/s from K = 64 to 768, where 4 tiles gave 4.3-5.1
-        constexpr int NT = 1;
-        if (K >= 320) {
-            constexpr int MT = 8;
-            int rblocks = (n + 4 * 16 * MT - 1) / (4 * 16 * MT);
-            hipLaunchKernelGGL((gemm_nn_kernel<MT, NT>), dim3(rblocks), dim3(256), 0, s, n, K, c, alpha, A, B, ldb,
-                               beta, C, ldc, vec_a);
-        } else {
-            constexpr int MT = 2;
-            int rblocks = (n + 4 * 16 * MT - 1) / (4 * 16 * MT);
-            hipLaunchKernelGGL((gemm_nn_kernel<MT, NT>), dim3(rblocks), dim3(256), 0, s, n, K, c, alpha, A, B, ldb,
-                               beta, C, ldc, vec_a);
-        }
+    const auto go = [&](auto kernel, int mt, int nt) {
+        const int rblocks = (n + 4 * 16 * mt - 1) / (4 * 16 * mt);
+        const int nct = (c + 16 * nt - 1) / (16 * nt);
+        hipLaunchKernelGGL(kernel, dim3(rblocks * nct), dim3(256), 0, s, n, K, c, alpha, A, B, ldb, beta, C, ldc,
+                           vec_a);
+    };
+    if (c > 16) {
+        go(gemm_nn_kernel<2, 4, false>, 2, 4);
     } else {
-        constexpr int MT = 2, NT = 4;
-        int rblocks = (n + 4 * 16 * MT - 1) / (4 * 16 * MT);
-        int nct = (c + 16 * NT - 1) / (16 * NT);
-        hipLaunchKernelGGL((gemm_nn_kernel<MT, NT>), dim3(rblocks * nct), dim3(256), 0, s, n, K, c, alpha, A, B,
-                           ldb, beta, C, ldc, vec_a);
+        const int mt = nn_row_tiles(K, c);
+        if (mt == 8)
+            go(gemm_nn_kernel<8, 1, false>, 8, 1);
+        else if (mt == 3)
+            go(gemm_nn_kernel<2, 1, true>, 2, 1);
+        else
+            go(gemm_nn_kernel<2, 1, false>, 2, 1);
     }
     return hipGetLastError();
 }

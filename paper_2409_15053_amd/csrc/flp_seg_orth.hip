@@ -1,26 +1,39 @@
-// Segmented block step for gfx950: the full reorthogonalisation (two passes
-// of classical Gram-Schmidt, Section 3.2.2) and the block normalisation
-// W = Q_{j+1} S_j (Cholesky QR twice, eq. lanczos) of many independent
-// solves, with one launch per stage for all of them.
+// The block step after the filter for gfx950: reorthogonalisation of the
+// filtered block (Section 3.2.2) and its normalisation W = Q_{j+1} S_j
+// (Cholesky QR twice, eq. lanczos), for one solve or for many independent
+// solves with one launch per stage.
 //
 // A launch's blocks are split into segments, one per solve, by a prefix of
 // block counts (OrthSeg tables); a block finds its segment with the same
-// ballot count as the segmented filter step.  The r x r Cholesky factors
-// are computed on the device (one lane per solve), so a whole block step
-// runs without a host round trip; a solve whose first factorisation finds
-// numerically dependent columns is flagged and skipped by the later stages,
-// and the host repairs it afterwards.
+// ballot count as the segmented filter step.  A single solve passes its
+// OrthSeg by value (ONE).  The r x r Cholesky factors are computed on the
+// device, so a whole block step runs without a host round trip; a solve that
+// needs the host (dependent columns, or another pass) is flagged and
+// skipped by the later stages, and the host repairs it afterwards.
+//
+// Reorthogonalisation: the filter is symmetric, so W = p(A) Q_j has
+// components of its own size only along Q_{j-1} and Q_j; those along the
+// older blocks are rounding (FP64) or the FP32 filter's error.  The first
+// pass of classical Gram-Schmidt therefore covers the last two blocks alone
+// (the local pass), the second the whole basis: the basis is read twice per
+// step, not four times.  The full pass leaves an orthogonality error of u
+// ||W_1|| / ||W_2|| (W_1 before, W_2 after it), so a column it takes more
+// than half of (||Q^T W_1|| > ||W_2||, seen from the coefficients and the
+// Gram matrix) flags the solve for another pass.
 //
 // Stages (c = block width r <= 16, k = basis columns, per solve):
-//   seg_tn_*    partial sums of Q^T W (k x c), or of W^T W (c x c), over row chunks
-//   seg_reduce  the partial sums in a fixed order -> H1, H2 or G
-//   seg_nn      W -= Q H (FP64 MFMA)
-//   seg_chol    D_j, Cholesky factor and its inverse (pass 1), or S_j (pass 2)
-//   seg_rscale  W <- W R^{-1}; the last one writes Q_{j+1} into the basis
-//               and the next filter input instead
+//   orth_local   partial sums of Q_loc^T W, Q_loc the basis columns kl .. k-1
+//   orth_reduce  the partial sums in a fixed order -> H, H2 or G
+//   orth_update  W -= Q_loc H, later W -= Q H2 with the partial Gram matrix
+//   orth_tn_*    partial sums of Q^T W (k x c)
+//   orth_chol    D_j, Cholesky factor and its inverse (pass 1), or S_j (pass 2)
+//   orth_gram    Gram matrix of W, or of W R1^{-1}
+//   orth_final   W R1^{-1} R2^{-1} -> the basis and the next filter input
 #include "flp_internal.h"
 #include "flp_device.h"
 #include "flp_gemm.h"
+
+#include <algorithm>
 
 namespace flp {
 
@@ -43,290 +56,576 @@ __device__ __forceinline__ int seg_of(const int *__restrict__ pre, int nseg, int
     return __builtin_amdgcn_readfirstlane(seg);
 }
 
-__device__ __forceinline__ bool flagged(const OrthSeg &e, int c) { return e.out[2 * c * c] != 0.0; }
+// The solve a block works for (*lb: the block's index within it).
+template <bool ONE>
+__device__ __forceinline__ OrthSeg my_seg(const OrthSeg *__restrict__ tab, const int *__restrict__ pre, int nseg,
+                                          const OrthSeg &one, int *lb) {
+    if constexpr (ONE) {
+        *lb = (int)blockIdx.x;
+        return one;
+    } else {
+        const int seg = seg_of(pre, nseg, blockIdx.x);
+        *lb = (int)blockIdx.x - pre[seg];
+        return tab[seg];
+    }
+}
 
-// Projection partial sums of Q^T W for solves with k > 128 on FMA: one
-// basis column per thread, 256 columns per block, the block's rows
-// [chunk * chunk_rows, ...) walked in step, so each W row is one wide load
-// through the scalar cache.  (This kernel has no LDS and no barrier: with
+__device__ __forceinline__ bool flagged(const OrthSeg &e, int c) { return as_global(e.out)[2 * c * c] != 0.0; }
+
+// The 4 waves' 16 x 16 sums (NA of them, D layout) added through LDS and
+// written as rows ti * 16 + i < K of dst (K x c).
+template <int NA>
+__device__ __forceinline__ void store_block_sum(dbl4 (&acc)[NA], int K, int c, double *dst, double (*red)[4][WAVE]) {
+    const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+        if (a * 16 >= K) break;  // uniform
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[wave][v][lane] = acc[a][v];
+        __syncthreads();
+        const int v = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
+        const double s = red[0][v][l] + red[1][v][l] + red[2][v][l] + red[3][v][l];
+        const int i = a * 16 + l / 16 + 4 * v, j = l % 16;
+        if (i < K && j < c) as_global_mut(dst)[(size_t)i * c + j] = s;
+        __syncthreads();
+    }
+}
+
+// Rows g .. g + 15 of W as the B operand of four MFMA steps (lane: row 4 t +
+// l/16, column l%16; zero outside rows < r1 and columns < c).
+__device__ __forceinline__ void load_w_rows(const double *W, int g, int r1, int c, double (&b)[4]) {
+    const int lane = threadIdx.x % WAVE, kr = lane / 16, m = lane % 16;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int row = g + 4 * t + kr;
+        const double x = as_global(W)[(int64_t)min(row, r1 - 1) * c + min(m, c - 1)];
+        b[t] = row < r1 && m < c ? x : 0.0;
+    }
+}
+
+// Partial sums over a block's rows of Q_loc^T W (columns kl .. k-1 of the
+// basis, at most 2 c + 15 < 48 of them; partial (k - kl) x c).  A wave takes
+// pieces of 16 rows, a load covers four rows.  Bound by the read of W and
+// Q_loc, which is strided by the panel's row of 1 KiB (110 us at n = 1e6, c =
+// 8: 2.9 TB/s).
+template <bool ONE>
+__global__ __launch_bounds__(256) void orth_local_kernel(const OrthSeg *__restrict__ tab,
+                                                         const int *__restrict__ pre, int nseg, const OrthSeg one,
+                                                         int c) {
+    __shared__ double red[4][4][WAVE];
+    int lb;
+    const OrthSeg e = my_seg<ONE>(tab, pre, nseg, one, &lb);
+    constexpr int NA = 3;
+    const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+    const int kr = lane / 16, m = lane % 16;
+    const int r0 = lb * e.lrows, r1 = min(e.n, r0 + e.lrows);
+    const int K = e.k - e.kl;
+    const double *qc[NA];
+#pragma unroll
+    for (int a = 0; a < NA; ++a) qc[a] = col_base(e.Q, e.kl + min(a * 16 + m, K - 1));
+    dbl4 acc[NA];
+#pragma unroll
+    for (int a = 0; a < NA; ++a) acc[a] = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int g = r0 + wave * 16; g < r1; g += 4 * 16) {
+        double b[4], q[NA][4];
+        load_w_rows(e.W, g, r1, c, b);
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+            if (a * 16 < K)  // uniform
+#pragma unroll
+                for (int t = 0; t < 4; ++t) q[a][t] = as_global(qc[a])[(int64_t)min(g + 4 * t + kr, r1 - 1) * e.Q.ld];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+                if (a * 16 < K) acc[a] = mfma16x16x4(q[a][t], b[t], acc[a]);
+    }
+    store_block_sum<NA>(acc, K, c, e.part + (size_t)lb * K * c, red);
+}
+
+// Partial sums of Q^T W (c = 8) on FMA: one basis column per thread and one
+// wavefront per block (a basis of 320 columns then has no idle threads), the
+// rows walked in step, so each W row is one wide load through the scalar
+// cache.  (This kernel has no LDS and no barrier: with
 // either in the same kernel the compiler can no longer prove the W rows
 // unmodified and falls back to per-lane vector loads of the same row.)
 // Partial sums of chunk t go to part[(t k + q) c + j].
-template <int CM, bool EXACT>
-__global__ __launch_bounds__(256) void seg_tn_fma_kernel(const OrthSeg *__restrict__ tab,
-                                                         const int *__restrict__ pre, int nseg, int c) {
-    const int seg = seg_of(pre, nseg, blockIdx.x);
-    const OrthSeg &e = tab[seg];
-    const int lb = blockIdx.x - pre[seg];
+template <bool ONE>
+__global__ __launch_bounds__(64) void orth_tn_fma_kernel(const OrthSeg *__restrict__ tab,
+                                                          const int *__restrict__ pre, int nseg, const OrthSeg one) {
+    constexpr int C = 8;
+    int lb;
+    const OrthSeg e = my_seg<ONE>(tab, pre, nseg, one, &lb);
     const int K = e.k;
-    const int ncb = (K + 255) / 256;
+    const int ncb = (K + WAVE - 1) / WAVE;
     const int cb = lb % ncb, chunk = lb / ncb;
-    const int q = cb * 256 + threadIdx.x;
+    const int q = cb * WAVE + threadIdx.x;
     if (q >= K) return;
-    const int r0 = chunk * e.chunk_rows, r1 = min(e.n, r0 + e.chunk_rows);
-    double acc[CM];
-    tn_fma_column<CM, (CM > 8 ? 4 : 8), EXACT>(as_global(col_base(e.Q, q)), e.Q.ld, r0, r1, as_global(e.W), c, acc,
-                                               c);
-    const auto d = as_global_mut(e.part) + ((size_t)chunk * K + q) * c;
+    const int r0 = chunk * e.prows, r1 = min(e.n, r0 + e.prows);
+    double acc[C];
+    tn_fma_column<C, 8>(as_global(col_base(e.Q, q)), e.Q.ld, r0, r1, as_global(e.W), C, acc);
+    const auto d = as_global_mut(e.part) + ((size_t)chunk * K + q) * C;
 #pragma unroll
-    for (int j = 0; j < CM; ++j)
-        if (EXACT || j < c) d[j] = acc[j];
+    for (int j = 0; j < C; ++j) d[j] = acc[j];
 }
 
-// Projection partial sums on FP64 MFMA (the layout of the single-solve
-// kernel: one B tile of 16 columns, NT A tiles per wave, 4 waves over the
-// rows of a chunk combined through LDS): Q^T W for solves with k <= 128
-// (NT = 8 covers the basis), or the Gram matrix W^T W (GRAM, NT = 2).
-template <bool GRAM>
-__global__ __launch_bounds__(256) void seg_tn_mfma_kernel(const OrthSeg *__restrict__ tab,
-                                                          const int *__restrict__ pre, int nseg, int c, int chk) {
-    constexpr int NT = GRAM ? 2 : 8;
+// The same on FP64 MFMA: one B tile of 16 columns, 8 A tiles (128 basis
+// columns) per block, 4 waves over the rows of a chunk combined through LDS.
+template <bool ONE>
+__global__ __launch_bounds__(256) void orth_tn_mfma_kernel(const OrthSeg *__restrict__ tab,
+                                                           const int *__restrict__ pre, int nseg, const OrthSeg one,
+                                                           int c) {
     __shared__ double red[4][4][WAVE];
-    const int seg = seg_of(pre, nseg, blockIdx.x);
-    const OrthSeg &e = tab[seg];
-    if (chk && flagged(e, c)) return;
-    const int chunk = blockIdx.x - pre[seg];
-    const int K = GRAM ? c : e.k;
-    const DMat A = GRAM ? DMat{e.W, c, 0, 30} : e.Q;
-    const int rows = GRAM ? e.gchunk_rows : e.chunk_rows;
-    const int r0 = chunk * rows;
-    // 16-byte A loads: the basis panels always qualify, W when c is even
-    const bool aligned = !GRAM || (c % 2 == 0);
-    tn_mfma_block<NT>(r0, min(e.n, r0 + rows), K, c, 0, 0, A, e.W, c, aligned, e.part + (size_t)chunk * K * c, red);
+    int lb;
+    const OrthSeg e = my_seg<ONE>(tab, pre, nseg, one, &lb);
+    const int ngrp = (e.k + 127) / 128;
+    const int chunk = lb / ngrp, grp = lb % ngrp;
+    const int r0 = chunk * e.prows;
+    tn_mfma_block<8>(r0, min(e.n, r0 + e.prows), e.k, c, grp * 128, 0, e.Q, e.W, c, true,
+                     e.part + (size_t)chunk * e.k * c, red);
 }
 
-// Sum of the per-chunk partials in a fixed order: 64 outputs per block, its
-// 4 thread rows split the chunks and combine through LDS.  which: 0 -> H1,
-// 1 -> H2 (k x c each), 2 -> G (c x c).
-__global__ __launch_bounds__(256) void seg_reduce_kernel(const OrthSeg *__restrict__ tab,
-                                                         const int *__restrict__ pre, int nseg, int c, int which,
-                                                         int chk) {
-    __shared__ double red[4][64];
-    const int seg = seg_of(pre, nseg, blockIdx.x);
-    const OrthSeg &e = tab[seg];
+// Sum of the per-chunk partials in a fixed order: 16 outputs per block, its
+// 16 thread rows split the chunks and combine through LDS.  which: 0 -> H,
+// 1 -> H2, 2 -> G from the updates' blocks, 3 -> G from the blocks over W.
+template <bool ONE>
+__global__ __launch_bounds__(256) void orth_reduce_kernel(const OrthSeg *__restrict__ tab,
+                                                          const int *__restrict__ pre, int nseg, const OrthSeg one,
+                                                          int c, int which, int chk) {
+    __shared__ double red[16][17];
+    int lb;
+    const OrthSeg e = my_seg<ONE>(tab, pre, nseg, one, &lb);
     if (chk && flagged(e, c)) return;
-    const int lb = blockIdx.x - pre[seg];
-    const int K = which == 2 ? c : e.k;
-    const int nch = which == 2 ? e.gnchunks : e.nchunks;
-    const auto dst = as_global_mut(which == 2 ? e.G : e.H + (size_t)which * e.k * c);
+    const int K = which == 0 ? e.k - e.kl : (which == 1 ? e.k : c);
+    const int nch = which == 1 ? e.pchunks : (which == 2 ? e.ublk : e.lblk);
+    const auto dst = as_global_mut(which == 0 ? e.H : (which == 1 ? e.H + (size_t)e.k * c : e.G));
     const int total = K * c;
-    const int tx = threadIdx.x % 64, ty = threadIdx.x / 64;
-    const int o = lb * 64 + tx;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
+    const int o = lb * 16 + tx;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
     if (o < total) {
         const auto p = as_global(e.part) + o;
         int q = ty;
-        for (; q + 12 < nch; q += 16) {
-            s0 += p[(size_t)q * total];
-            s1 += p[(size_t)(q + 4) * total];
-            s2 += p[(size_t)(q + 8) * total];
-            s3 += p[(size_t)(q + 12) * total];
+        for (; q + 112 < nch; q += 128) {
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = p[(size_t)(q + 16 * u) * total];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s[u % 4] += x[u];
         }
-        for (; q < nch; q += 4) s0 += p[(size_t)q * total];
+        for (; q < nch; q += 16) s[0] += p[(size_t)q * total];
     }
-    red[ty][tx] = (s0 + s1) + (s2 + s3);
+    red[ty][tx] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
-    if (ty == 0 && o < total) dst[o] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
+    if (ty == 0 && o < total) {
+        double t = 0.0;
+#pragma unroll
+        for (int y = 0; y < 16; ++y) t += red[y][tx];
+        dst[o] = t;
+    }
 }
 
-// W -= Q H_which (k inner), 256 rows per block.
-__global__ __launch_bounds__(256) void seg_nn_kernel(const OrthSeg *__restrict__ tab, const int *__restrict__ pre,
-                                                     int nseg, int c, int which) {
-    const int seg = seg_of(pre, nseg, blockIdx.x);
-    const OrthSeg &e = tab[seg];
-    const int lb = blockIdx.x - pre[seg];
-    gemm_nn_rows<4, 1>(e.n, e.k, c, -1.0, e.Q, e.H + (size_t)which * e.k * c, c, 1.0, e.W, c, true, lb, 0);
+// W -= Q_loc H (LOCAL) or W -= Q H2 with the partial Gram matrix of the
+// result (its rows sit in the D layout, which is the operand layout of
+// W^T W, so it costs no further read).  MT row tiles of 16 rows per wave and
+// turn.  Bound by the read of the basis.
+template <bool ONE, bool LOCAL, int MT, bool PIPE>
+__global__ __launch_bounds__(256) void orth_update_kernel(const OrthSeg *__restrict__ tab,
+                                                          const int *__restrict__ pre, int nseg, const OrthSeg one,
+                                                          int c) {
+    __shared__ double red[4][4][WAVE];
+    int lb;
+    const OrthSeg e = my_seg<ONE>(tab, pre, nseg, one, &lb);
+    const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+    const int kq = lane / 16, m = lane % 16;
+    const int r0 = lb * e.urows, r1 = min(e.n, r0 + e.urows);
+    const int K = LOCAL ? e.k - e.kl : e.k;
+    const double *H = LOCAL ? e.H : e.H + (size_t)e.k * c;
+    dbl4 gacc[1] = {dbl4{0.0, 0.0, 0.0, 0.0}};
+    for (int row0 = r0 + wave * 16 * MT; row0 < r1; row0 += 4 * 16 * MT) {
+        dbl4 acc[MT][1];
+        gemm_nn_acc<MT, 1, PIPE>(r1, K, c, e.Q, H, c, true, row0, 0, acc, LOCAL ? e.kl : 0);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = row0 + 16 * i + kq + 4 * v;
+                double w2 = 0.0;
+                if (row < r1 && m < c) {
+                    const auto wp = as_global_mut(e.W) + (int64_t)row * c + m;
+                    w2 = *wp - acc[i][0][v];
+                    *wp = w2;
+                }
+                if constexpr (!LOCAL) gacc[0] = mfma16x16x4(w2, w2, gacc[0]);
+            }
+    }
+    if constexpr (!LOCAL) store_block_sum<1>(gacc, c, c, e.part + (size_t)lb * c * c, red);
 }
 
-// The r x r factorisations of one solve on one wavefront, through LDS.
-// Pass 1: D_j = sym(diagonal blocks of H1 + H2) to out[0, c^2); the first
-// factor R1 of G (upper, row-major) by right-looking Cholesky with the
-// block QR's dependent-column rule (a pivot at or below (1e-7 ||W||_F)^2
-// marks the column: status 1, the later launches skip the solve and the host
-// repairs it), then R1^{-1}.  Pass 2: the second factor R2 (status 2 if it
-// breaks down), R2^{-1} and S_j = R2 R1 to out[c^2, 2 c^2).  Lane j computes
-// column j of an inverse; the other steps spread the c x c entries over the
-// lanes.
-__global__ __launch_bounds__(64) void seg_chol_kernel(const OrthSeg *__restrict__ tab, int c, int pass) {
-    __shared__ double M[16 * 16], T[16 * 16];
-    __shared__ int bad;
-    const OrthSeg &e = tab[blockIdx.x];
-    const int lane = threadIdx.x;
+// Lane `from`'s value, uniform over the wavefront.
+__device__ __forceinline__ double lane_value(double x, int from) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, from);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), from);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// The r x r factorisations of one solve.  Pass 1: D_j = sym(diagonal blocks
+// of H + H2) to out[0, c^2); the first factor R1 of G (upper, row-major) by
+// right-looking Cholesky with the block QR's dependent-column rule (a pivot
+// at or below (1e-7 ||W||_F)^2 marks the column: status 1), then R1^{-1};
+// status 3 where the full pass took more of a column than it left
+// (||H2_j||^2 > G_jj).  Pass 2: the second factor R2 (status 2 if it breaks
+// down), R2^{-1} and S_j = R2 R1 to out[c^2, 2 c^2).  k = 0: normalisation
+// alone.  The four waves share the column sums of H2; the factorisation is a
+// serial chain that the first wave runs in registers: lane j holds column j
+// of the matrix, padded to 16 x 16 with the identity, and the entries a step
+// needs from other columns come by readlane (5 us at c = 16; the same steps
+// through LDS took 24).
+template <bool ONE>
+__global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restrict__ tab, const OrthSeg one, int c,
+                                                        int pass) {
+    __shared__ double sq[16][16];
+    const OrthSeg e = ONE ? one : tab[blockIdx.x];
     const int cc = c * c;
     double *out = e.out;
     double *status = out + 2 * cc;
     if (pass == 2 && *status != 0.0) return;  // uniform: every lane reads the same flag
-    if (pass == 1) {
-        const double *h1 = e.H + (size_t)(e.k - c) * c;
-        const double *h2 = e.H + (size_t)e.k * c + (size_t)(e.k - c) * c;
-        for (int t = lane; t < cc; t += WAVE) {
-            const int i = t / c, j = t % c;
-            const double a = h1[i * c + j] + h2[i * c + j], b = h1[j * c + i] + h2[j * c + i];
-            out[t] = 0.5 * (a + b);
+    const bool orth = pass == 1 && e.k > 0;
+    if (orth) {
+        // column sums of squares of H2: thread (ty, tx) takes rows ty, ty + 16, ... of column tx
+        const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
+        const auto h = as_global(e.H) + (size_t)e.k * c;
+        double s = 0.0;
+        if (tx < c) {
+            int q = ty;
+            for (; q + 112 < e.k; q += 128) {
+                double x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = h[(size_t)(q + 16 * u) * c + tx];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s = fma(x[u], x[u], s);
+            }
+            for (; q < e.k; q += 16) s = fma(h[(size_t)q * c + tx], h[(size_t)q * c + tx], s);
         }
+        sq[ty][tx] = s;
     }
-    for (int t = lane; t < cc; t += WAVE) M[t] = e.G[t];
-    if (lane == 0) bad = 0;
     __syncthreads();
+    if (threadIdx.x >= WAVE) return;
+    const int lane = threadIdx.x, j = lane % 16;
+    const bool col = lane < c;
+    double M[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        M[i] = (i < c && j < c) ? as_global(e.G)[min(i, c - 1) * c + min(j, c - 1)] : (i == j ? 1.0 : 0.0);
+    bool again = false;
+    if (orth) {
+        const auto h1 = as_global(e.H) + (size_t)(e.k - e.kl - c) * c;
+        const auto h2 = as_global(e.H) + (size_t)e.k * c + (size_t)(e.k - c) * c;
+        if (col)
+            for (int i = 0; i < c; ++i) {
+                const double a = h1[i * c + j] + h2[i * c + j], b = h1[j * c + i] + h2[j * c + i];
+                out[i * c + j] = 0.5 * (a + b);
+            }
+        double s = 0.0, g = 0.0;
+#pragma unroll
+        for (int y = 0; y < 16; ++y) s += sq[y][j];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) g = i == j ? M[i] : g;
+        again = __ballot(col && s > g) != 0ull;
+    }
     double thr2 = 1e-300;
     if (pass == 1) {
         double fro2 = 0.0;
-        for (int i = 0; i < c; ++i) fro2 += fmax(M[i * c + i], 0.0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (i < c) fro2 += fmax(lane_value(M[i], i), 0.0);
         const double thr = 1e-7 * sqrt(fro2);
         thr2 = fmax(thr * thr, 1e-300);
     }
-    // right-looking Cholesky in place: row k of M becomes row k of R
-    for (int k = 0; k < c; ++k) {
-        const double d = M[k * c + k];
-        const bool ok = d > thr2;
+    // right-looking Cholesky: M[i] becomes row i of R
+    bool bad = false;
+    double inv[16];  // 1 / R[i][i], uniform
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const double d = lane_value(M[k], k);
+        const bool ok = k >= c || d > thr2;
+        bad = bad || !ok;
         const double rkk = ok ? sqrt(d) : 1.0;
-        __syncthreads();
-        if (lane == 0) {
-            M[k * c + k] = rkk;
-            if (!ok) bad = 1;
+        inv[k] = 1.0 / rkk;
+        M[k] = j == k ? rkk : (j > k && ok ? M[k] / rkk : 0.0);
+#pragma unroll
+        for (int i = k + 1; i < 16; ++i) {
+            const double f = lane_value(M[k], i);
+            M[i] = fma(-f, M[k], M[i]);
         }
-        for (int j = k + 1 + lane; j < c; j += WAVE) M[k * c + j] = ok ? M[k * c + j] / rkk : 0.0;
-        __syncthreads();
-        // trailing update of the upper triangle: M[i][j] -= R[k][i] R[k][j]
-        for (int t = lane; t < cc; t += WAVE) {
-            const int i = t / c, j = t % c;
-            if (i > k && j >= i) M[t] -= M[k * c + i] * M[k * c + j];
-        }
-        __syncthreads();
     }
-    // lower triangle of R is zero
-    for (int t = lane; t < cc; t += WAVE)
-        if (t / c > t % c) M[t] = 0.0;
-    __syncthreads();
-    if (bad) {
-        if (lane == 0) *status = pass == 1 ? 1.0 : 2.0;
+    if (bad || again) {
+        if (lane == 0) *status = pass == 2 ? kOrthBreakdown : (again ? kOrthAgain : kOrthDependent);
         return;
     }
-    // Ri = R^{-1}: lane j solves for column j by back substitution
-    if (lane < c) {
-        const int j = lane;
-        for (int i = c - 1; i >= 0; --i) {
-            double t = (i == j) ? 1.0 : 0.0;
-            if (i <= j)
-                for (int k = i + 1; k <= j; ++k) t -= M[i * c + k] * T[k * c + j];
-            T[i * c + j] = i <= j ? t / M[i * c + i] : 0.0;
+    // column j of R^{-1} by back substitution
+    double T[16];
+#pragma unroll
+    for (int i = 15; i >= 0; --i) {
+        double t = i == j ? 1.0 : 0.0;
+#pragma unroll
+        for (int k = i + 1; k < 16; ++k) t = fma(-lane_value(M[i], k), T[k], t);
+        T[i] = t * inv[i];
+    }
+    double *Ri = pass == 1 ? e.Ri1 : e.Ri2;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        if (i < c && col) {
+            if (pass == 1) as_global_mut(e.R1)[i * c + j] = M[i];
+            as_global_mut(Ri)[i * c + j] = T[i];
         }
-    }
-    __syncthreads();
-    double *Rk = pass == 1 ? e.R1 : e.R2;
-    for (int t = lane; t < cc; t += WAVE) {
-        Rk[t] = M[t];
-        e.Ri[t] = T[t];
-    }
     if (pass == 1) {
-        if (lane == 0) *status = 0.0;
+        if (lane == 0) *status = kOrthOk;
         return;
     }
     // S_j = R2 R1 (both upper triangular)
     double *Sj = out + cc;
-    for (int t = lane; t < cc; t += WAVE) {
-        const int i = t / c, j = t % c;
+    double R1[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) R1[i] = i < c && j < c ? as_global(e.R1)[min(i, c - 1) * c + min(j, c - 1)] : 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
         double acc = 0.0;
-        for (int k = i; k <= j; ++k) acc += M[i * c + k] * e.R1[k * c + j];
-        Sj[t] = acc;
+#pragma unroll
+        for (int k = i; k < 16; ++k) acc = fma(lane_value(M[i], k), R1[k], acc);
+        if (i < c && col) Sj[i * c + j] = acc;
     }
 }
 
-// W <- W Ri row by row (one row per thread).  final: the result is the new
-// basis block Q_{j+1}: it goes to the basis columns k .. k + c - 1 (when
-// they exist) and to the next filter input (FP64 and, if present, FP32).
-template <int CM, bool EXACT>
-__global__ __launch_bounds__(256) void seg_rscale_kernel(const OrthSeg *__restrict__ tab,
-                                                         const int *__restrict__ pre, int nseg, int c, int final_) {
-    const int seg = seg_of(pre, nseg, blockIdx.x);
-    const OrthSeg &e = tab[seg];
+// An upper-triangular r x r matrix R as an MFMA operand: R[4 (l/16) + q][l%16]
+// for step q (the permuted k index of load_w_cols), zero outside c x c.
+__device__ __forceinline__ void load_tri(const double *R, int c, double (&b)[4]) {
+    const int lane = threadIdx.x % WAVE, kq = lane / 16, m = lane % 16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int i = 4 * kq + q;
+        const double x = as_global(R)[min(i, c - 1) * c + min(m, c - 1)];
+        b[q] = i < c && m < c ? x : 0.0;
+    }
+}
+
+// Row g + l%16 of W, columns 4 (l/16) .. + 3 (zero outside rows < r1 and
+// columns < c): an operand with the rows on l%16.  Two 16-byte loads where
+// the four columns exist together (they need no more than element alignment).
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ void load_w_cols(const double *W, int g, int r1, int c, double (&a)[4]) {
+    const int lane = threadIdx.x % WAVE, kq = lane / 16, m = lane % 16;
+    const auto p = as_global(W) + (int64_t)min(g + m, r1 - 1) * c;
+    const bool row = g + m < r1;
+    if ((c & 3) == 0) {
+        const int c0 = min(4 * kq, c - 4);
+        const dbl2u x0 = *reinterpret_cast<gptr<dbl2u>>(p + c0);
+        const dbl2u x1 = *reinterpret_cast<gptr<dbl2u>>(p + c0 + 2);
+        const bool in = row && 4 * kq < c;
+        a[0] = in ? x0.x : 0.0;
+        a[1] = in ? x0.y : 0.0;
+        a[2] = in ? x1.x : 0.0;
+        a[3] = in ? x1.y : 0.0;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double x = p[min(4 * kq + q, c - 1)];
+            a[q] = row && 4 * kq + q < c ? x : 0.0;
+        }
+    }
+}
+
+// Partial sums of the Gram matrix of Y = W R1^{-1} (FIRST: of W, with the
+// identity in R1^{-1}'s place): a wave forms 16 rows of Y with four MFMA
+// steps, and Y's D layout is the operand layout of Y^T Y.  Y itself is not
+// written (orth_final forms it again), so this reads W once, in 16-byte
+// pieces.
+template <bool ONE, bool FIRST>
+__global__ __launch_bounds__(256) void orth_gram_kernel(const OrthSeg *__restrict__ tab, const int *__restrict__ pre,
+                                                        int nseg, const OrthSeg one, int c) {
+    __shared__ double red[4][4][WAVE];
+    int lb;
+    const OrthSeg e = my_seg<ONE>(tab, pre, nseg, one, &lb);
+    if (!FIRST && flagged(e, c)) return;
+    const int wave = threadIdx.x / WAVE;
+    const int r0 = lb * e.lrows, r1 = min(e.n, r0 + e.lrows);
+    double ri[4];
+    if constexpr (FIRST) {
+        const int lane = threadIdx.x % WAVE;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ri[q] = 4 * (lane / 16) + q == lane % 16 ? 1.0 : 0.0;
+    } else {
+        load_tri(e.Ri1, c, ri);
+    }
+    dbl4 gacc[1] = {dbl4{0.0, 0.0, 0.0, 0.0}};
+    for (int g = r0 + wave * 64; g < r1; g += 4 * 64) {
+        double a[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load_w_cols(e.W, g + 16 * u, r1, c, a[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            dbl4 y = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y = mfma16x16x4(a[u][q], ri[q], y);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) gacc[0] = mfma16x16x4(y[v], y[v], gacc[0]);
+        }
+    }
+    store_block_sum<1>(gacc, c, c, e.part + (size_t)lb * c * c, red);
+}
+
+// Q_{j+1} = (W R1^{-1}) R2^{-1}: the first product transposed (R1^{-T} W^T,
+// operands exchanged), whose D layout has the rows on l%16 as the second
+// product's operand wants them.  The result goes to the basis columns k ..
+// k + c - 1 (when they exist) and to the next filter input (FP64 and, if
+// present, FP32), or over W itself (Vin = W: a wave reads its rows before it
+// writes them).
+template <bool ONE>
+__global__ __launch_bounds__(256) void orth_final_kernel(const OrthSeg *__restrict__ tab,
+                                                         const int *__restrict__ pre, int nseg, const OrthSeg one,
+                                                         int c) {
+    int lb;
+    const OrthSeg e = my_seg<ONE>(tab, pre, nseg, one, &lb);
     if (flagged(e, c)) return;
-    const int row = (blockIdx.x - pre[seg]) * 256 + threadIdx.x;
-    if (row >= e.n) return;
-    double x[CM], y[CM];
-    const auto w = as_global(e.W) + (int64_t)row * c;
+    const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+    const int kq = lane / 16, m = lane % 16;
+    const int r0 = lb * e.lrows, r1 = min(e.n, r0 + e.lrows);
+    double r1i[4], r2i[4];
+    load_tri(e.Ri1, c, r1i);
 #pragma unroll
-    for (int j = 0; j < CM; ++j) x[j] = (EXACT || j < c) ? w[j] : 0.0;
-    const auto Ri = as_global(e.Ri);
-#pragma unroll
-    for (int j = 0; j < CM; ++j) {
-        double t = 0.0;
-#pragma unroll
-        for (int i = 0; i <= j; ++i)
-            if (EXACT || j < c) t = fma(x[i], Ri[i * c + j], t);
-        y[j] = t;
+    for (int v = 0; v < 4; ++v) {  // R2^{-1}[l/16 + 4 v][l%16]
+        const int i = kq + 4 * v;
+        const double x = as_global(e.Ri2)[min(i, c - 1) * c + min(m, c - 1)];
+        r2i[v] = i < c && m < c ? x : 0.0;
     }
-    if (!final_) {
-        const auto wo = as_global_mut(e.W) + (int64_t)row * c;
+    const bool basis = e.k + c <= e.qcap;
+    double *qc = basis && m < c ? const_cast<double *>(col_base(e.Q, e.k + m)) : nullptr;
+    for (int g = r0 + wave * 64; g < r1; g += 4 * 64) {
+        double a[4][4];
 #pragma unroll
-        for (int j = 0; j < CM; ++j)
-            if (EXACT || j < c) wo[j] = y[j];
-        return;
-    }
-    if (e.k + c <= e.qcap) {
+        for (int u = 0; u < 4; ++u) load_w_cols(e.W, g + 16 * u, r1, c, a[u]);
 #pragma unroll
-        for (int j = 0; j < CM; ++j)
-            if (EXACT || j < c) as_global_mut(const_cast<double *>(col_base(e.Q, e.k + j)))[(int64_t)row * e.Q.ld] = y[j];
-    }
-    const auto vo = as_global_mut(e.Vin) + (int64_t)row * c;
+        for (int u = 0; u < 4; ++u) {
+            dbl4 y = dbl4{0.0, 0.0, 0.0, 0.0}, z = dbl4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int j = 0; j < CM; ++j)
-        if (EXACT || j < c) vo[j] = y[j];
-    if (e.V32) {
-        const auto fo = as_global_mut(e.V32) + (int64_t)row * c;
+            for (int q = 0; q < 4; ++q) y = mfma16x16x4(r1i[q], a[u][q], y);
 #pragma unroll
-        for (int j = 0; j < CM; ++j)
-            if (EXACT || j < c) fo[j] = (float)y[j];
+            for (int v = 0; v < 4; ++v) z = mfma16x16x4(y[v], r2i[v], z);
+            if (m < c) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t row = g + 16 * u + kq + 4 * v;
+                    if (row < r1) {
+                        as_global_mut(e.Vin)[row * c + m] = z[v];
+                        if (basis) as_global_mut(qc)[row * e.Q.ld] = z[v];
+                        if (e.V32) as_global_mut(e.V32)[row * c + m] = (float)z[v];
+                    }
+                }
+            }
+        }
     }
 }
 
-template <int CM, bool EXACT>
-hipError_t launch_seg_orth_t(const OrthPlan &p, int c, hipStream_t s) {
+template <bool ONE>
+void launch_qr(const OrthPlan &p, const int *const *pre, int c, bool have_gram, hipStream_t s) {
+    const OrthSeg *tab = p.tab;
+    const int ns = p.nseg;
+#define FLP_ORTH(K, KIND, ...)     hipLaunchKernelGGL(K, dim3(p.blocks[KIND]), dim3(256), 0, s, tab, pre[KIND], ns, p.one, c, ##__VA_ARGS__)
+    if (!have_gram) FLP_ORTH((orth_gram_kernel<ONE, true>), kOrthLocal);
+    FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, have_gram ? 2 : 3, 0);
+    hipLaunchKernelGGL((orth_chol_kernel<ONE>), dim3(ns), dim3(256), 0, s, tab, p.one, c, 1);
+    FLP_ORTH((orth_gram_kernel<ONE, false>), kOrthLocal);
+    FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, 3, 1);
+    hipLaunchKernelGGL((orth_chol_kernel<ONE>), dim3(ns), dim3(256), 0, s, tab, p.one, c, 2);
+    FLP_ORTH((orth_final_kernel<ONE>), kOrthLocal);
+}
+
+template <bool ONE>
+hipError_t launch_all(const OrthPlan &p, int c, hipStream_t s) {
     const OrthSeg *tab = p.tab;
     const int ns = p.nseg;
     const int *pre[kOrthKinds];
-    for (int t = 0; t < kOrthKinds; ++t) pre[t] = p.pre + (size_t)t * ns;
-    for (int pass = 0; pass < 2; ++pass) {
-        if (p.blocks[kOrthFma] > 0)
-            hipLaunchKernelGGL((seg_tn_fma_kernel<CM, EXACT>), dim3(p.blocks[kOrthFma]), dim3(256), 0, s, tab,
-                               pre[kOrthFma], ns, c);
-        if (p.blocks[kOrthMfma] > 0)
-            hipLaunchKernelGGL(seg_tn_mfma_kernel<false>, dim3(p.blocks[kOrthMfma]), dim3(256), 0, s, tab,
-                               pre[kOrthMfma], ns, c, 0);
-        hipLaunchKernelGGL(seg_reduce_kernel, dim3(p.blocks[kOrthRed]), dim3(256), 0, s, tab, pre[kOrthRed], ns, c,
-                           pass, 0);
-        hipLaunchKernelGGL(seg_nn_kernel, dim3(p.blocks[kOrthRows]), dim3(256), 0, s, tab, pre[kOrthRows], ns, c,
-                           pass);
-    }
-    for (int pass = 1; pass <= 2; ++pass) {
-        const int chk = pass == 2;
-        hipLaunchKernelGGL(seg_tn_mfma_kernel<true>, dim3(p.blocks[kOrthGram]), dim3(256), 0, s, tab,
-                           pre[kOrthGram], ns, c, chk);
-        hipLaunchKernelGGL(seg_reduce_kernel, dim3(p.blocks[kOrthGred]), dim3(256), 0, s, tab, pre[kOrthGred], ns,
-                           c, 2, chk);
-        hipLaunchKernelGGL(seg_chol_kernel, dim3(ns), dim3(WAVE), 0, s, tab, c, pass);
-        hipLaunchKernelGGL((seg_rscale_kernel<CM, EXACT>), dim3(p.blocks[kOrthRows]), dim3(256), 0, s, tab,
-                           pre[kOrthRows], ns, c, pass == 2 ? 1 : 0);
-    }
+    for (int t = 0; t < kOrthKinds; ++t) pre[t] = ONE ? nullptr : p.pre + (size_t)t * ns;
+    FLP_ORTH((orth_local_kernel<ONE>), kOrthLocal);
+    FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedL, 0, 0);
+    if (p.mt == 1)
+        FLP_ORTH((orth_update_kernel<ONE, true, 1, false>), kOrthUpd);
+    else
+        FLP_ORTH((orth_update_kernel<ONE, true, 4, false>), kOrthUpd);
+    if (p.blocks[kOrthFma] > 0)
+        hipLaunchKernelGGL((orth_tn_fma_kernel<ONE>), dim3(p.blocks[kOrthFma]), dim3(WAVE), 0, s, tab, pre[kOrthFma],
+                           ns, p.one);
+    if (p.blocks[kOrthMfma] > 0) FLP_ORTH((orth_tn_mfma_kernel<ONE>), kOrthMfma);
+    FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedH, 1, 0);
+    if (p.mt == 8)
+        FLP_ORTH((orth_update_kernel<ONE, false, 8, false>), kOrthUpd);
+    else if (p.mt == 3)
+        FLP_ORTH((orth_update_kernel<ONE, false, 2, true>), kOrthUpd);
+    else if (p.mt == 2)
+        FLP_ORTH((orth_update_kernel<ONE, false, 2, false>), kOrthUpd);
+    else
+        FLP_ORTH((orth_update_kernel<ONE, false, 1, true>), kOrthUpd);
+    launch_qr<ONE>(p, pre, c, true, s);
     return hipGetLastError();
+#undef FLP_ORTH
 }
 
 }  // namespace
 
+int orth_row_tiles(int64_t rows, int kmax, int c) {
+    // a few blocks' worth of rows: one tile per wave, so all of them have work
+    if (rows < 64 * 512) return 1;
+    return nn_row_tiles(kmax, c);
+}
+
+void orth_split(OrthSeg &e, int c, int mt, int wgs, int (&blocks)[kOrthKinds]) {
+    const auto up = [](int64_t x, int64_t g) { return (int)((x + g - 1) / g * g); };
+    const auto cdiv = [](int64_t x, int64_t y) { return (int)((x + y - 1) / y); };
+    const int n = e.n;
+    e.lrows = std::max(128, up(cdiv(n, wgs), 64));
+    e.lblk = cdiv(n, e.lrows);
+    blocks[kOrthLocal] += e.lblk;
+    blocks[kOrthRedG] += cdiv(c * c, 16);
+    if (e.k == 0) return;  // normalisation alone
+    const int ug = mt == 1 ? 64 : (mt == 8 ? 512 : 256);
+    e.urows = up(cdiv(n, 2 * wgs), ug);
+    e.ublk = cdiv(n, e.urows);
+    blocks[kOrthUpd] += e.ublk;
+    blocks[kOrthRedL] += cdiv((int64_t)(e.k - e.kl) * c, 16);
+    e.fma = tn_use_fma(e.k, c);
+    const int groups = e.fma ? (e.k + WAVE - 1) / WAVE : (e.k + 127) / 128;
+    const int grain = e.fma ? 64 : 128;
+    const size_t cap = wgs >= 1024 ? (size_t)32 << 20 : (size_t)4 << 20;  // doubles of partial sums
+    e.prows = std::max(grain, up(cdiv(n, std::max(1, (e.fma ? 4 * wgs : 2 * wgs) / groups)), grain));
+    if (!e.fma) e.prows = std::max(e.prows, up(cdiv(n, 512), grain));
+    while ((size_t)cdiv(n, e.prows) * e.k * c > cap) e.prows *= 2;
+    e.pchunks = cdiv(n, e.prows);
+    blocks[e.fma ? kOrthFma : kOrthMfma] += e.pchunks * groups;
+    blocks[kOrthRedH] += cdiv((int64_t)e.k * c, 16);
+}
+
+size_t orth_part_elems(const OrthSeg &e, int c) {
+    size_t m = (size_t)e.lblk * c * c;
+    if (e.k > 0) {
+        m = std::max(m, (size_t)e.lblk * (e.k - e.kl) * c);
+        m = std::max(m, (size_t)e.ublk * c * c);
+        m = std::max(m, (size_t)e.pchunks * e.k * c);
+    }
+    return m;
+}
+
 hipError_t launch_seg_orth(const OrthPlan &p, int c, hipStream_t s) {
     if (p.nseg <= 0) return hipSuccess;
-    switch (c) {
-    case 1: return launch_seg_orth_t<1, true>(p, c, s);
-    case 2: return launch_seg_orth_t<2, true>(p, c, s);
-    case 3: return launch_seg_orth_t<4, false>(p, c, s);
-    case 4: return launch_seg_orth_t<4, true>(p, c, s);
-    case 5: case 6: case 7: return launch_seg_orth_t<8, false>(p, c, s);
-    case 8: return launch_seg_orth_t<8, true>(p, c, s);
-    case 16: return launch_seg_orth_t<16, true>(p, c, s);
-    default:
-        if (c >= 9 && c <= 15) return launch_seg_orth_t<16, false>(p, c, s);
-        return hipErrorInvalidValue;
-    }
+    if (c < 1 || c > 16) return hipErrorInvalidValue;
+    return p.tab ? launch_all<false>(p, c, s) : launch_all<true>(p, c, s);
+}
+
+hipError_t launch_block_qr(const OrthPlan &p, int c, hipStream_t s) {
+    if (c < 1 || c > 16 || p.tab || p.nseg != 1) return hipErrorInvalidValue;
+    const int *pre[kOrthKinds] = {};
+    launch_qr<true>(p, pre, c, false, s);
+    return hipGetLastError();
 }
 
 }  // namespace flp

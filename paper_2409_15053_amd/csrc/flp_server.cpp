@@ -63,7 +63,7 @@ size_t footprint(const flp_csr &A, const flp_opts &o) {
     if (fp32) b += n * r * 4 + (A.val32 ? 0 : (size_t)A.nnz * 4);
     // sliced ELL copy of A (AUTO keeps it within 1.25x the nonzeros)
     if (o.format != FLP_FORMAT_CSR) b += (size_t)(1.25 * (double)A.nnz + 64.0) * (fp32 ? 8 : 12) + n / 16 + 8;
-    b += (2 * cols * r + 4 * r * r + 64) * 8;
+    b += (2 * cols * r + 6 * r * r + 64) * 8;
     return b;
 }
 

@@ -109,12 +109,11 @@ int solve_setup(Solve &S) {
     CK(ensure(B.W, sizeof(double) * (size_t)n * r));
     CK(ensure(B.Vin, sizeof(double) * (size_t)n * r));
     const size_t hcols = (size_t)(S.npanels << kPanelLog2);
-    CK(ensure(B.hdev, sizeof(double) * (2 * hcols * r + 4 * (size_t)r * r + 64)));
+    CK(ensure(B.hdev, sizeof(double) * (2 * hcols * r + 6 * (size_t)r * r + 64)));
     S.W = (double *)B.W.p;
     S.Vin = (double *)B.Vin.p;
     S.hdev = (double *)B.hdev.p;
     S.gdev = S.hdev + 2 * hcols * r;
-    S.rdev = S.gdev + (size_t)r * r;
     if (!S.pin) CK(hipHostMalloc((void **)&S.pin, sizeof(double) * 4 * (size_t)r * r, hipHostMallocDefault));
     S.Q = panel_mat((double *)B.Q.p, n, kPanelLog2);
     const size_t es = fp32 ? sizeof(float) : sizeof(double);
@@ -170,75 +169,77 @@ int ensure_basis(Solve &S, int64_t cols) {
     return FLP_OK;
 }
 
+void orth_seg(const Solve &S, OrthSeg &e) {
+    const size_t rr = (size_t)S.r * S.r;
+    e = OrthSeg{};
+    e.n = S.n;
+    e.k = (S.steps + 1) * S.r;  // basis columns so far
+    e.kl = orth_local_first(e.k, S.r);
+    e.qcap = (int)(S.qpanels << kPanelLog2);
+    e.Q = S.Q;
+    e.W = S.W;
+    e.H = S.hdev;
+    e.G = S.gdev;
+    e.R1 = S.gdev + rr;
+    e.Ri1 = S.gdev + 2 * rr;
+    e.Ri2 = S.gdev + 3 * rr;
+    e.out = S.gdev + 4 * rr;
+    e.Vin = S.Vin;
+    e.V32 = S.V32;
+}
+
+void orth_account(Solve &S) {
+    const int k = (S.steps + 1) * S.r;
+    S.st.filter_bytes += filter_step_bytes(S.n, S.A->nnz, S.r, S.o.prec) * S.filt->m;
+    S.st.mv += (int64_t)S.r * S.filt->m;
+    // the local pass and the full one, each reading its columns twice
+    S.st.orth_bytes += 2.0 * 8.0 * (double)S.n * (k + (k - orth_local_first(k, S.r)));
+}
+
 int step_orth_launch(Solve &S) {
-    const int n = S.n, r = S.r;
+    const int r = S.r;
     CKR(ensure_basis(S, (int64_t)(S.steps + 2) * r));  // the projection's columns and the next block
-    hipStream_t s = S.s;
     S.t_step0 = now();
-    const int k = (S.steps + 1) * r;  // basis columns so far
-    S.st.filter_bytes += filter_step_bytes(n, S.A->nnz, r, S.o.prec) * S.filt->m;
-    S.st.mv += (int64_t)r * S.filt->m;
-    S.st.orth_bytes += 4.0 * 8.0 * (double)n * k;
-    // full reorthogonalisation (Section 3.2.2): two passes of classical Gram-Schmidt
-    CKR(cgs2(S.Q, k, n, S.W, r, S.hdev, s));
-    const size_t rr = (size_t)r * r;
-    CK(hipMemcpyAsync(S.pin, S.hdev + (size_t)(k - r) * r, sizeof(double) * rr, hipMemcpyDeviceToHost, s));
-    CK(hipMemcpyAsync(S.pin + rr, S.hdev + (size_t)k * r + (size_t)(k - r) * r, sizeof(double) * rr,
-                      hipMemcpyDeviceToHost, s));
-    // Gram matrix of the projected block (first Cholesky QR pass)
-    CKR(gram_tn(n, r, r, plain_mat(S.W, r), S.W, r, S.gdev, nullptr, s));
-    CK(hipMemcpyAsync(S.pin + 2 * rr, S.gdev, sizeof(double) * rr, hipMemcpyDeviceToHost, s));
+    orth_account(S);
+    OrthPlan p{};
+    p.nseg = 1;
+    orth_seg(S, p.one);
+    p.mt = orth_row_tiles(S.n, p.one.k, r);
+    orth_split(p.one, r, p.mt, 1024, p.blocks);
+    Buf &pb = ws().partials;
+    CK(ensure_grow(pb, sizeof(double) * orth_part_elems(p.one, r)));
+    p.one.part = (double *)pb.p;
+    CK(launch_seg_orth(p, r, S.s));
+    CK(hipMemcpyAsync(S.pin, p.one.out, sizeof(double) * (2 * (size_t)r * r + 1), hipMemcpyDeviceToHost, S.s));
     return FLP_OK;
 }
 
-int step_qr1(Solve &S) {
-    const int n = S.n, r = S.r;
-    hipStream_t s = S.s;
+int step_orth_take(Solve &S, const double *out) {
+    const int r = S.r, k = (S.steps + 1) * r;
     const size_t rr = (size_t)r * r;
-    const double *h1 = S.pin, *h2 = S.pin + rr, *G = S.pin + 2 * rr;
-    for (int i = 0; i < r; ++i)
-        for (int j = 0; j < r; ++j) {
-            const double a = h1[i * r + j] + h2[i * r + j], b = h1[j * r + i] + h2[j * r + i];
-            S.D_all.push_back(0.5 * (a + b));
+    const int status = (int)out[2 * rr];
+    if (status == kOrthBreakdown) return fail(FLP_E_DEVICE, "block QR: second Cholesky pass broke down");
+    S.D_all.insert(S.D_all.end(), out, out + rr);
+    if (status == kOrthOk) {
+        S.Sj.assign(out + rr, out + 2 * rr);
+    } else {
+        // the synchronous repair paths on the projected block, then the
+        // copies that the kernels skipped
+        if (status == kOrthAgain) {
+            CKR(cgs2(S.Q, k, S.n, S.W, r, S.hdev, S.s));
+            std::vector<double> h(2 * rr);
+            for (int pass = 0; pass < 2; ++pass)
+                CK(hipMemcpyAsync(h.data() + pass * rr, S.hdev + (size_t)pass * k * r + (size_t)(k - r) * r,
+                                  sizeof(double) * rr, hipMemcpyDeviceToHost, S.s));
+            CK(hipStreamSynchronize(S.s));
+            double *D = &S.D_all[S.D_all.size() - rr];
+            for (int i = 0; i < r; ++i)
+                for (int j = 0; j < r; ++j)
+                    D[i * r + j] += 0.5 * ((h[i * r + j] + h[rr + i * r + j]) + (h[j * r + i] + h[rr + j * r + i]));
         }
-    // W = Q_{j+1} S_j (eq. lanczos) by Cholesky QR twice
-    double fro2 = 0.0;
-    for (int i = 0; i < r; ++i) fro2 += std::max(G[i * r + i], 0.0);
-    const double thr = 1e-7 * std::sqrt(fro2);
-    std::vector<int> bad;
-    cholesky_flag(r, G, std::max(thr * thr, 1e-300), S.R1, bad);
-    S.slow = false;
-    for (int i = 0; i < r; ++i) S.slow = S.slow || bad[i];
-    if (S.slow) {
-        // numerically dependent columns: the synchronous repair path
-        const int k = (S.steps + 1) * r;
-        return block_qr_impl(S.W, n, r, &S.Q, k, S.Sj, S.o.seed, 1000 + S.steps, s, nullptr);
-    }
-    std::vector<double> Ri;
-    upper_inverse(r, S.R1, Ri);
-    std::memcpy(S.pin + 3 * rr, Ri.data(), sizeof(double) * rr);
-    CK(hipMemcpyAsync(S.rdev, S.pin + 3 * rr, sizeof(double) * rr, hipMemcpyHostToDevice, s));
-    CK(launch_gemm_nn(n, r, r, 1.0, plain_mat(S.W, r), S.rdev, r, 0.0, S.W, r, s));
-    CKR(gram_tn(n, r, r, plain_mat(S.W, r), S.W, r, S.gdev, nullptr, s));
-    CK(hipMemcpyAsync(S.pin + 2 * rr, S.gdev, sizeof(double) * rr, hipMemcpyDeviceToHost, s));
-    return FLP_OK;
-}
-
-int step_qr2(Solve &S) {
-    const int n = S.n, r = S.r;
-    hipStream_t s = S.s;
-    const size_t rr = (size_t)r * r;
-    if (!S.slow) {
-        std::vector<double> R2, Ri;
-        std::vector<int> bad;
-        cholesky_flag(r, S.pin + 2 * rr, 1e-300, R2, bad);
-        for (int i = 0; i < r; ++i)
-            if (bad[i]) return fail(FLP_E_DEVICE, "block QR: second Cholesky pass broke down");
-        upper_inverse(r, R2, Ri);
-        std::memcpy(S.pin + 3 * rr, Ri.data(), sizeof(double) * rr);
-        CK(hipMemcpyAsync(S.rdev, S.pin + 3 * rr, sizeof(double) * rr, hipMemcpyHostToDevice, s));
-        CK(launch_gemm_nn(n, r, r, 1.0, plain_mat(S.W, r), S.rdev, r, 0.0, S.W, r, s));
-        matmul_upper(r, R2, S.R1, S.Sj);
+        CKR(block_qr_impl(S.W, S.n, r, &S.Q, k, S.Sj, S.o.seed, 1000 + S.steps, S.s, nullptr));
+        if (k + r <= (int)(S.qpanels << kPanelLog2)) CK(launch_copy_block(S.n, r, 1.0, S.W, r, S.Q, k, nullptr, 0, S.s));
+        CK(launch_copy_block(S.n, r, 1.0, S.W, r, plain_mat(S.Vin, r), 0, S.V32, r, S.s));
     }
     S.S_all.insert(S.S_all.end(), S.Sj.begin(), S.Sj.end());
     ++S.steps;
@@ -391,7 +392,7 @@ int wait_check(Solve &S) {
     return FLP_OK;
 }
 
-int step_check(Solve &S, bool async, bool copy_next) {
+int step_check(Solve &S, bool async) {
     // a check that has finished in the background is applied first; one
     // still running after kMaxSpeculative further block steps is waited for
     // (speculative steps are wasted work if it decides convergence)
@@ -425,20 +426,13 @@ int step_check(Solve &S, bool async, bool copy_next) {
             if (S.done) return FLP_OK;
         }
     }
-    if (!copy_next) return FLP_OK;
-    // the new block joins the basis and is the next filter input
-    const int n = S.n, r = S.r, k = S.steps * r;
-    CK(launch_copy_block(n, r, 1.0, S.W, r, S.Q, k, nullptr, 0, S.s));
-    CK(launch_copy_block(n, r, 1.0, S.W, r, plain_mat(S.Vin, r), 0, S.V32, r, S.s));
     return FLP_OK;
 }
 
 int solve_after_filter(Solve &S) {
     CKR(step_orth_launch(S));
     CK(hipStreamSynchronize(S.s));
-    CKR(step_qr1(S));
-    CK(hipStreamSynchronize(S.s));
-    CKR(step_qr2(S));
+    CKR(step_orth_take(S, S.pin));
     return step_check(S);
 }
 
