@@ -449,7 +449,36 @@ int solve_batch_impl(int count, const flp_csr *const *A, const double *alpha, co
         S.o.stream = nullptr;
         jobs[i] = std::move(j);
     }
-    // Set-up (bounds estimate, filter, buffers, start block) is a chain of
+    // The bounds estimates of all solves as one run with shared launches
+    // (each alone is a chain of about 120 launches that a small matrix cannot
+    // fill); what cannot be estimated here is left to its own set-up.
+    {
+        std::vector<BoundsRun> runs;
+        std::vector<Solve *> of;
+        for (auto &j : jobs) {
+            Solve &S = *j->S;
+            if (check_csr(S.A) != FLP_OK || solve_args(S) != FLP_OK || S.o.lmin < S.o.lmax || S.o.sym_tol >= 0.0)
+                continue;
+            BoundsRun b;
+            b.A = S.A;
+            b.k0 = S.o.k0 > 0 ? S.o.k0 : kDefaultK0;
+            b.seed = S.o.seed;
+            runs.push_back(b);
+            of.push_back(&S);
+        }
+        const double tb = now();
+        const int rb = estimate_bounds_many(runs, E.s);
+        if (rb != FLP_OK && rb != FLP_E_NOMEM) return rb;
+        ws().W.release();  // the vectors of all matrices at once
+        for (size_t i = 0; rb == FLP_OK && i < runs.size(); ++i) {
+            if (runs[i].code != FLP_OK) continue;  // its own set-up reports it
+            of[i]->lmin = runs[i].lmin;
+            of[i]->lmax = runs[i].lmax;
+            of[i]->st.t_pre = now() - tb;
+            of[i]->have_bounds = true;
+        }
+    }
+    // Set-up (filter, buffers, start block) is a chain of
     // small launches and host round trips per solve: the solves' set-ups run
     // on a few threads at once, each with a stream of its own (the threads'
     // workspaces are released when they join), and join the engine in order.

@@ -62,6 +62,25 @@ __host__ __device__ __forceinline__ int chunk_tile(int b, int G, int chunk, int 
     return (s / chunk) * span + x * chunk + s % chunk;
 }
 
+// SplitMix64 (Steele, Lea & Flood, OOPSLA 2014): the output function applied
+// to a Weyl sequence; used here as a counter-based generator.
+__device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
+    x += 0x9E3779B97F4A7C15ull;
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+    return x ^ (x >> 31);
+}
+
+// Entry idx of the N(0, 1) sequence (seed, sid): 53-bit uniforms in (0, 1] and
+// [0, 1), Box-Muller.
+__device__ __forceinline__ double normal_at(uint64_t seed, uint64_t sid, uint64_t idx) {
+    const uint64_t key = splitmix64(seed ^ splitmix64(sid));
+    const uint64_t u1 = splitmix64(key + 2 * idx), u2 = splitmix64(key + 2 * idx + 1);
+    const double a = ((u1 >> 11) + 1) * (1.0 / 9007199254740992.0);
+    const double b = (u2 >> 11) * (1.0 / 9007199254740992.0);
+    return sqrt(-2.0 * log(a)) * cospi(2.0 * b);
+}
+
 template <typename T, int VEC>
 struct Vec;
 template <>

@@ -992,53 +992,19 @@ int block_qr_impl(double *W, int n, int r, const DMat *Q, int k, std::vector<dou
 
 // ------------------------------------------------------------------ bounds
 
-int estimate_bounds_impl(const flp_csr *A, int k0, uint64_t seed, double *lmin, double *lmax, hipStream_t s,
-                         const flp_csr *spmv_A) {
-    Workspace &w = ws();
-    const int n = A->n;
-    int k = std::max(1, std::min(k0, n));
-    // The last two Lanczos vectors, row-major n x 2: q_j in column j % 2 (the
-    // next vector overwrites q_{j-1}); w = A q_j is orthogonalised twice
-    // against both (the three-term recurrence, with its rounding removed
-    // twice), which keeps the extreme Ritz values and their residual bounds
-    // that the bounds need without the cost of a full basis.
-    CK(ensure(w.Q, sizeof(double) * (size_t)n * 2));
-    CK(ensure(w.W, sizeof(double) * (size_t)n * 2));
-    double *Qw = (double *)w.Q.p, *wv = (double *)w.W.p;
-    double *dev = nullptr;
-    CKR(small_dev((size_t)2 * k + 64, &dev));
-    // start vector
-    CK(launch_randn(n, 1, wv, 1, seed, 0xB0B0, s));
-    double g = 0.0;
-    CKR(gram_tn(n, 1, 1, plain_mat(wv, 1), wv, 1, dev, &g, s));
-    if (!(g > 0.0)) return fail(FLP_E_DEVICE, "bounds: zero start vector");
-    CK(launch_copy_block(n, 1, 1.0 / std::sqrt(g), wv, 1, plain_mat(Qw, 2), 0, nullptr, 0, s));
-    // k steps without a host round trip: the Gram-Schmidt coefficients, the
-    // norm and the next vector stay on the device (dev: H1, H2 in [0, 4),
-    // ||w||^2 at 8, alpha_j / beta_j pairs from 16)
-    double *gdev = dev + 8, *abdev = dev + 16;
-    const flp_csr *M = spmv_A ? spmv_A : A;
-    for (int j = 0; j < k; ++j) {
-        const int cur = j % 2, kk = std::min(j + 1, 2);
-        // w = A q_j
-        CK(launch_cheb_step<double, double>(n, M->rowptr, M->colind, M->val, 1, Qw + cur, 2, nullptr, 0, nullptr, 0,
-                                            wv, 1, 1.0, 0.0, 0.0, 0.0, s, StepShape{}, spmv_A != nullptr));
-        CKR(cgs2(plain_mat(Qw, 2), kk, n, wv, 1, dev, s));
-        CKR(gram_tn(n, 1, 1, plain_mat(wv, 1), wv, 1, gdev, nullptr, s));
-        CK(launch_lanczos_next(n, wv, Qw + (1 - cur), 2, gdev, dev, dev + kk, kk == 1 ? 0 : cur, j, abdev, s));
-    }
-    std::vector<double> ab(2 * (size_t)k);
-    CK(hipMemcpyAsync(ab.data(), abdev, sizeof(double) * ab.size(), hipMemcpyDeviceToHost, s));
-    CK(hipStreamSynchronize(s));
+namespace {
+// Bounds from a Lanczos run's coefficients (LanczosSeg::ab).
+int bounds_from_run(int k, const double *ab, double *lmin, double *lmax) {
+    if (!(ab[0] > 0.0)) return fail(FLP_E_DEVICE, "bounds: zero start vector");
     // the recurrence ends at the first breakdown (beta_j = 0) or after k steps
     std::vector<double> al, be;
     double beta_k = 0.0;
     int steps = 0;
     for (int j = 0; j < k; ++j) {
-        al.push_back(ab[2 * j]);
-        be.push_back(ab[2 * j + 1]);
+        al.push_back(ab[2 * j + 1]);
+        be.push_back(ab[2 * j + 2]);
         steps = j + 1;
-        beta_k = ab[2 * j + 1];
+        beta_k = ab[2 * j + 2];
         if (beta_k == 0.0) break;
     }
     // Ritz values of the tridiagonal and the last eigenvector row
@@ -1060,21 +1026,94 @@ int estimate_bounds_impl(const flp_csr *A, int k0, uint64_t seed, double *lmin, 
     double lo = theta[0] - rho_lo - delta;
     double hi = theta[steps - 1] + rho_hi + delta;
     // Gershgorin enclosure
-    int nb = gershgorin_blocks(n);
-    CK(ensure(w.partials, sizeof(double) * (2 * (size_t)nb + 8)));
-    CKR(small_dev((size_t)2 * k + 64, &dev));
-    CK(launch_gershgorin(n, A->rowptr, A->colind, A->val, (double *)w.partials.p, nb, dev, s));
-    double gg[2];
-    CK(hipMemcpyAsync(gg, dev, sizeof(gg), hipMemcpyDeviceToHost, s));
-    CK(hipStreamSynchronize(s));
-    *lmin = std::max(lo, gg[0]);
-    *lmax = std::min(hi, gg[1]);
+    *lmin = std::max(lo, ab[2 * k + 1]);
+    *lmax = std::min(hi, ab[2 * k + 2]);
     if (!(*lmin < *lmax)) {
         // a matrix with a single distinct eigenvalue: widen symmetrically
         double mid = 0.5 * (*lmin + *lmax), rad = std::max(1e-12, 1e-8 * std::fabs(mid));
         *lmin = mid - rad;
         *lmax = mid + rad;
     }
+    return FLP_OK;
+}
+}  // namespace
+
+int estimate_bounds_many(std::vector<BoundsRun> &runs, hipStream_t s) {
+    if (runs.empty()) return FLP_OK;
+    const size_t ns = runs.size();
+    // One device block: the vectors, partial sums and coefficients of every
+    // matrix, then the table.  The last Lanczos vectors suffice: w = A q_j is
+    // orthogonalised twice against q_j and q_{j-1} (the three-term recurrence,
+    // with its rounding removed twice), which keeps the extreme Ritz values
+    // and their residual bounds that the bounds need without a full basis.
+    std::vector<LanczosSeg> seg(ns);
+    std::vector<size_t> voff(ns), aoff(ns);
+    size_t elems = 0, abs_ = 0;
+    int blocks = 0, kmax = 0;
+    for (size_t i = 0; i < ns; ++i) {
+        const BoundsRun &b = runs[i];
+        LanczosSeg &e = seg[i];
+        e = LanczosSeg{};
+        e.n = b.A->n;
+        e.k = std::max(1, std::min(b.k0, e.n));
+        e.seed = b.seed;
+        lanczos_split(e);
+        e.blk0 = blocks;
+        blocks += e.nb;
+        kmax = std::max(kmax, e.k);
+        const flp_csr *M = b.sell ? b.sell : b.A;
+        e.sell = b.sell ? 1 : 0;
+        e.rowptr = M->rowptr;
+        e.colind = M->colind;
+        e.val = M->val;
+        e.grow = b.A->rowptr;
+        e.gcol = b.A->colind;
+        e.gval = b.A->val;
+        voff[i] = elems;
+        elems += 3 * (size_t)e.n + 8 * (size_t)kLanczosBlocks;
+        aoff[i] = abs_;
+        abs_ += 2 * (size_t)e.k + 4;
+    }
+    const size_t tab = sizeof(LanczosSeg) * ns;
+    Buf &buf = ws().W;
+    CK(ensure(buf, sizeof(double) * (elems + abs_) + tab));
+    double *base = (double *)buf.p, *abd = base + elems;
+    for (size_t i = 0; i < ns; ++i) {
+        LanczosSeg &e = seg[i];
+        double *p = base + voff[i];
+        for (int t = 0; t < 3; ++t) e.z[t] = p + (size_t)t * e.n;
+        e.part = p + 3 * (size_t)e.n;
+        e.gersh = e.part + 6 * (size_t)kLanczosBlocks;
+        e.ab = abd + aoff[i];
+    }
+    if (ns == 1) {
+        CK(launch_lanczos(nullptr, 1, seg[0], blocks, kmax, s));
+    } else {
+        CK(h2d(abd + abs_, seg.data(), tab, s));
+        CK(launch_lanczos((const LanczosSeg *)(abd + abs_), (int)ns, LanczosSeg{}, blocks, kmax, s));
+    }
+    double *h = nullptr;
+    CKR(pinned_scratch(abs_, &h));
+    CK(hipMemcpyAsync(h, abd, sizeof(double) * abs_, hipMemcpyDeviceToHost, s));
+    CK(hipStreamSynchronize(s));
+    for (size_t i = 0; i < ns; ++i) {
+        BoundsRun &b = runs[i];
+        b.code = bounds_from_run(seg[i].k, h + aoff[i], &b.lmin, &b.lmax);
+    }
+    return FLP_OK;
+}
+
+int estimate_bounds_impl(const flp_csr *A, int k0, uint64_t seed, double *lmin, double *lmax, hipStream_t s,
+                         const flp_csr *spmv_A) {
+    std::vector<BoundsRun> run(1);
+    run[0].A = A;
+    run[0].sell = spmv_A;
+    run[0].k0 = k0;
+    run[0].seed = seed;
+    CKR(estimate_bounds_many(run, s));
+    CKR(run[0].code);
+    *lmin = run[0].lmin;
+    *lmax = run[0].lmax;
     return FLP_OK;
 }
 

@@ -268,6 +268,16 @@ int block_qr_impl(double *W, int n, int r, const DMat *Q, int k, std::vector<dou
 // sliced ELL copy of A with FP64 values for the products, or NULL (CSR A).
 int estimate_bounds_impl(const flp_csr *A, int k0, uint64_t seed, double *lmin, double *lmax, hipStream_t s,
                          const flp_csr *spmv_A = nullptr);
+// The same for many matrices with one launch per stage (flp_bounds.hip).
+struct BoundsRun {
+    const flp_csr *A = nullptr;
+    const flp_csr *sell = nullptr;  // its sliced ELL copy with FP64 values, or null
+    int k0 = 0;
+    uint64_t seed = 0;
+    double lmin = 0, lmax = 0;  // out
+    int code = FLP_OK;          // out
+};
+int estimate_bounds_many(std::vector<BoundsRun> &runs, hipStream_t s);
 int orthonormalize_cols(int n, int c, double *&Y, double *&tmp, int ldc, double *sdev, hipStream_t s);
 // The same for a block Y whose columns need not be orthonormal (Y itself is
 // left as it is): replaces orthonormalising Y and then rayleigh_ritz.
@@ -329,6 +339,7 @@ struct Solve {
     SolveBufs *B = nullptr;
     // derived
     int n = 0, r = 0;
+    bool have_bounds = false;  // lmin, lmax and st.t_pre are set before the set-up (a batch's shared estimate)
     double lmin = 0, lmax = 0, tau = 0, tol_p = 0;
     bool unfiltered = false;  // p(Ahat) = Ahat (plain block Lanczos)
     bool sell = false;        // the filter reads A's sliced ELL copy SA (values sval32 in FP32)
@@ -371,6 +382,8 @@ struct Solve {
     ~Solve();
 };
 
+// argument checks of a filtered or plain solve
+int solve_args(const Solve &S);
 // bounds, filter, buffers, start block (PREPROC and set-up)
 int solve_setup(Solve &S);
 // Grows the basis allocation (by doubling, on S.s, synchronous) so that it

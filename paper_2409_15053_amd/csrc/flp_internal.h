@@ -260,11 +260,27 @@ hipError_t launch_reduce_partials(const TnPlan &pl, int K, int c, const double *
 hipError_t launch_gemm_nn(int n, int K, int c, double alpha, DMat A, const double *B, int64_t ldb, double beta,
                           double *C, int64_t ldc, hipStream_t s);
 
-// Gershgorin: lo/hi per block into part (2 * nblocks doubles), then reduced
-// to out[0] = min(a_ii - R_i), out[1] = max(a_ii + R_i).
-hipError_t launch_gershgorin(int n, const int32_t *rowptr, const int32_t *colind, const double *val,
-                             double *part, int part_cap, double *out, hipStream_t s);
-int gershgorin_blocks(int n);
+// One matrix's part of the bounds estimate's Lanczos run (flp_bounds.hip);
+// every pointer is device memory.
+constexpr int kLanczosBlocks = 1024;  // most blocks (partial sums per stage) of one matrix
+struct LanczosSeg {
+    int n, k;                // rows; Lanczos steps
+    int rows, nb, blk0;      // rows per block and blocks (lanczos_split); first block in a shared launch
+    int sell;                // 1: rowptr / colind / val are a sliced ELL copy
+    uint64_t seed;           // of the start vector
+    const int32_t *rowptr, *colind;  // what the products read A in
+    const double *val;
+    const int32_t *grow, *gcol;      // A in CSR (Gershgorin rows)
+    const double *gval;
+    double *z[3];            // the last vectors, n each
+    double *part, *gersh;    // 6 kLanczosBlocks and 2 kLanczosBlocks doubles
+    double *ab;              // out: beta_0, alpha_0, ..., beta_k, then Gershgorin low and high (2 k + 3)
+};
+void lanczos_split(LanczosSeg &e);
+// The run of every matrix in tab (device array of nseg, sorted by blk0;
+// blocks in all), or of `one` (tab null).
+hipError_t launch_lanczos(const LanczosSeg *tab, int nseg, const LanczosSeg &one, int blocks, int kmax,
+                          hipStream_t s);
 // *bad += entries a_ij of A without a stored a_ji within tol (relative); *bad
 // must be zeroed first.  Columns must be sorted within each row.
 hipError_t launch_sym_check(int n, const int32_t *rowptr, const int32_t *colind, const double *val, double tol,
@@ -280,10 +296,6 @@ hipError_t launch_randn(int rows, int cols, double *out, int64_t ld, uint64_t se
 hipError_t launch_copy_block(int rows, int cols, double scale, const double *src, int64_t lds, DMat dst, int dcol0,
                              float *dst32, int64_t ldd32, hipStream_t s);
 hipError_t launch_to_float(int64_t count, const double *src, float *dst, hipStream_t s);
-// alpha_j, beta_j and q_{j+1} of a single-vector Lanczos step (bounds
-// estimate); q_j's coefficients at h1[hj], h2[hj]
-hipError_t launch_lanczos_next(int n, const double *w, double *q, int64_t ldq, const double *g, const double *h1,
-                               const double *h2, int hj, int j, double *ab, hipStream_t s);
 hipError_t launch_scale(int64_t count, double a, const double *src, double *dst, hipStream_t s);
 
 // resid[j] = || AX[:, j] - lam[j] X[:, j] ||_2 for row-major n x c blocks

@@ -4,8 +4,8 @@
 //   reorthogonalisation (Section 3.2.2): the update and wide projections on
 //   FP64 MFMA (16x16x4), the projection against at most 16 columns on FMA
 //   (2 flops per byte: bandwidth-bound either way).
-// * small helpers: Gershgorin bounds, counter-based normal generator,
-//   block copies, residual norms.
+// * small helpers: counter-based normal generator, block copies, residual
+//   norms.
 #include "flp_internal.h"
 #include "flp_device.h"
 #include "flp_gemm.h"
@@ -260,100 +260,12 @@ __global__ void sym_check_kernel(int n, const int32_t *__restrict__ rowptr, cons
     if (cnt) atomicAdd(bad, cnt);
 }
 
-__global__ void gershgorin_kernel(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colind,
-                                  const double *__restrict__ val, double *__restrict__ part) {
-    __shared__ double slo[256], shi[256];
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    double lo = 1e308, hi = -1e308;
-    if (i < n) {
-        double d = 0.0, rad = 0.0;
-        for (int p = rowptr[i]; p < rowptr[i + 1]; ++p) {
-            if (colind[p] == i)
-                d += val[p];
-            else
-                rad += fabs(val[p]);
-        }
-        lo = d - rad;
-        hi = d + rad;
-    }
-    slo[threadIdx.x] = lo;
-    shi[threadIdx.x] = hi;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            slo[threadIdx.x] = fmin(slo[threadIdx.x], slo[threadIdx.x + w]);
-            shi[threadIdx.x] = fmax(shi[threadIdx.x], shi[threadIdx.x + w]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = slo[0];
-        part[2 * blockIdx.x + 1] = shi[0];
-    }
-}
-
-__global__ void minmax_kernel(int m, const double *__restrict__ part, double *__restrict__ out) {
-    __shared__ double slo[256], shi[256];
-    double lo = 1e308, hi = -1e308;
-    for (int i = threadIdx.x; i < m; i += blockDim.x) {
-        lo = fmin(lo, part[2 * i]);
-        hi = fmax(hi, part[2 * i + 1]);
-    }
-    slo[threadIdx.x] = lo;
-    shi[threadIdx.x] = hi;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            slo[threadIdx.x] = fmin(slo[threadIdx.x], slo[threadIdx.x + w]);
-            shi[threadIdx.x] = fmax(shi[threadIdx.x], shi[threadIdx.x + w]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[0] = slo[0];
-        out[1] = shi[0];
-    }
-}
-
-// SplitMix64 (Steele, Lea & Flood, OOPSLA 2014): the output function applied
-// to a Weyl sequence; used here as a counter-based generator.
-__device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
-    x += 0x9E3779B97F4A7C15ull;
-    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
-    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-    return x ^ (x >> 31);
-}
-
 __global__ void randn_kernel(int rows, int cols, double *__restrict__ out, int64_t ld, uint64_t seed,
                              uint64_t sid) {
     int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t total = (int64_t)rows * cols;
     if (idx >= total) return;
-    uint64_t key = splitmix64(seed ^ splitmix64(sid));
-    uint64_t u1 = splitmix64(key + 2 * (uint64_t)idx);
-    uint64_t u2 = splitmix64(key + 2 * (uint64_t)idx + 1);
-    // 53-bit uniforms in (0, 1] and [0, 1); Box-Muller
-    double a = ((u1 >> 11) + 1) * (1.0 / 9007199254740992.0);
-    double b = (u2 >> 11) * (1.0 / 9007199254740992.0);
-    double z = sqrt(-2.0 * log(a)) * cospi(2.0 * b);
-    out[(idx / cols) * ld + idx % cols] = z;
-}
-
-// End of one step of the bounds estimate's single-vector Lanczos, on the
-// device: alpha_j = h1[hj] + h2[hj] (the two Gram-Schmidt passes' coefficient
-// of q_j, column hj of the projection), beta_j = sqrt(g) with g = ||w||^2,
-// and q_{j+1} = w / beta_j (zero after a breakdown, beta_j = 0).  ab[2j],
-// ab[2j+1] receive alpha_j, beta_j.
-__global__ void lanczos_next_kernel(int n, const double *__restrict__ w, double *__restrict__ q, int64_t ldq,
-                                    const double *__restrict__ g, const double *__restrict__ h1,
-                                    const double *__restrict__ h2, int hj, int j, double *__restrict__ ab) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const double beta = sqrt(fmax(g[0], 0.0));
-    if (i == 0) {
-        ab[2 * j] = h1[hj] + h2[hj];
-        ab[2 * j + 1] = beta;
-    }
-    if (i < n) q[(int64_t)i * ldq] = beta > 0.0 ? w[i] / beta : 0.0;
+    out[(idx / cols) * ld + idx % cols] = normal_at(seed, sid, (uint64_t)idx);
 }
 
 __global__ void copy_block_kernel(int rows, int cols, double scale, const double *__restrict__ src, int64_t lds,
@@ -477,21 +389,10 @@ __global__ void transpose_in_kernel(int n, int c, const double *__restrict__ src
 
 }  // namespace
 
-int gershgorin_blocks(int n) { return (n + 255) / 256; }
-
 hipError_t launch_sym_check(int n, const int32_t *rowptr, const int32_t *colind, const double *val, double tol,
                             unsigned int *bad, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(sym_check_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, rowptr, colind, val, tol, bad);
-    return hipGetLastError();
-}
-
-hipError_t launch_gershgorin(int n, const int32_t *rowptr, const int32_t *colind, const double *val, double *part,
-                             int part_cap, double *out, hipStream_t s) {
-    int nb = gershgorin_blocks(n);
-    if (nb > part_cap) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(gershgorin_kernel, dim3(nb), dim3(256), 0, s, n, rowptr, colind, val, part);
-    hipLaunchKernelGGL(minmax_kernel, dim3(1), dim3(256), 0, s, nb, part, out);
     return hipGetLastError();
 }
 
@@ -509,13 +410,6 @@ hipError_t launch_copy_block(int rows, int cols, double scale, const double *src
     if (total == 0) return hipSuccess;
     hipLaunchKernelGGL(copy_block_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, rows, cols, scale,
                        src, lds, dst, dcol0, dst32, ldd32);
-    return hipGetLastError();
-}
-
-hipError_t launch_lanczos_next(int n, const double *w, double *q, int64_t ldq, const double *g, const double *h1,
-                               const double *h2, int hj, int j, double *ab, hipStream_t s) {
-    hipLaunchKernelGGL(lanczos_next_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, w, q, ldq, g, h1, h2, hj, j,
-                       ab);
     return hipGetLastError();
 }
 

@@ -40,6 +40,21 @@ void assemble_T(const Solve &S, int steps, std::vector<double> &T) {
 
 }  // namespace
 
+int solve_args(const Solve &S) {
+    const flp_opts &o = S.o;
+    const int n = S.A->n, r = o.block;
+    if (r < 1 || r > 16) return fail(FLP_E_ARG, "block size must be in [1, 16]");
+    if (r > n) return fail(FLP_E_ARG, "block size exceeds n");
+    if (!(std::isfinite(S.alpha) && std::isfinite(S.beta)) || !(S.alpha < S.beta))
+        return fail(FLP_E_ARG, "need finite alpha < beta");
+    if (o.prec != FLP_PREC_FP64 && o.prec != FLP_PREC_FP32_FILTER) return fail(FLP_E_ARG, "bad precision");
+    if (o.format != FLP_FORMAT_AUTO && o.format != FLP_FORMAT_CSR && o.format != FLP_FORMAT_SELL)
+        return fail(FLP_E_ARG, "bad storage format");
+    if (o.unfiltered && o.prec == FLP_PREC_FP32_FILTER) return fail(FLP_E_ARG, "unfiltered Lanczos runs in FP64 only");
+    if (o.warm || o.warm_count != 0) return fail(FLP_E_ARG, "a warm start runs through flp_solve only");
+    return FLP_OK;
+}
+
 int solve_setup(Solve &S) {
     S.t_start = now();
     const flp_csr *A = S.A;
@@ -48,17 +63,9 @@ int solve_setup(Solve &S) {
     S.n = A->n;
     S.r = o.block;
     const int n = S.n, r = S.r;
-    if (r < 1 || r > 16) return fail(FLP_E_ARG, "block size must be in [1, 16]");
-    if (r > n) return fail(FLP_E_ARG, "block size exceeds n");
-    if (!(std::isfinite(S.alpha) && std::isfinite(S.beta)) || !(S.alpha < S.beta))
-        return fail(FLP_E_ARG, "need finite alpha < beta");
-    if (o.prec != FLP_PREC_FP64 && o.prec != FLP_PREC_FP32_FILTER) return fail(FLP_E_ARG, "bad precision");
+    CKR(solve_args(S));
     const bool fp32 = o.prec == FLP_PREC_FP32_FILTER;
     S.unfiltered = o.unfiltered != 0;
-    if (o.format != FLP_FORMAT_AUTO && o.format != FLP_FORMAT_CSR && o.format != FLP_FORMAT_SELL)
-        return fail(FLP_E_ARG, "bad storage format");
-    if (S.unfiltered && fp32) return fail(FLP_E_ARG, "unfiltered Lanczos runs in FP64 only");
-    if (o.warm || o.warm_count != 0) return fail(FLP_E_ARG, "a warm start runs through flp_solve only");
     if (o.sym_tol >= 0.0) CKR(check_symmetric(A, o.sym_tol, s));
 
     // the filter's storage of A (and, in FP64, the bounds' SpMVs read it too)
@@ -72,14 +79,16 @@ int solve_setup(Solve &S) {
 
     // PREPROC: spectrum bounds
     double t0 = now();
-    if (o.lmin < o.lmax) {
-        S.lmin = o.lmin;
-        S.lmax = o.lmax;
-    } else {
-        CKR(estimate_bounds_impl(A, o.k0 > 0 ? o.k0 : kDefaultK0, o.seed, &S.lmin, &S.lmax, s,
-                                 S.sell && !fp32 ? &S.SA : nullptr));
+    if (!S.have_bounds) {
+        if (o.lmin < o.lmax) {
+            S.lmin = o.lmin;
+            S.lmax = o.lmax;
+        } else {
+            CKR(estimate_bounds_impl(A, o.k0 > 0 ? o.k0 : kDefaultK0, o.seed, &S.lmin, &S.lmax, s,
+                                     S.sell && !fp32 ? &S.SA : nullptr));
+        }
+        S.st.t_pre = now() - t0;
     }
-    S.st.t_pre = now() - t0;
 
     flp_filter *pf = nullptr;
     CKR(make_filter(S.alpha, S.beta, S.unfiltered ? 1 : o.degree, S.lmin, S.lmax, o.eps > 0 ? o.eps : kDefaultEps,
