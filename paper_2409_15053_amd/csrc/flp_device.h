@@ -81,88 +81,56 @@ __device__ __forceinline__ double normal_at(uint64_t seed, uint64_t sid, uint64_
     return sqrt(-2.0 * log(a)) * cospi(2.0 * b);
 }
 
+// A piece of VEC elements of at most 16 bytes, aligned to its elements only:
+// a global access of up to 16 bytes needs no more than 4-byte alignment on
+// gfx950, so block widths and leading dimensions that are no multiple of 16
+// bytes are read and written in whole pieces too.
 template <typename T, int VEC>
-struct Vec;
-template <>
-struct Vec<double, 1> {
-    using type = double;
-};
-template <>
-struct Vec<double, 2> {
-    using type = double2;
-};
-template <>
-struct Vec<float, 1> {
-    using type = float;
-};
-template <>
-struct Vec<float, 2> {
-    using type = float2;
-};
-template <>
-struct Vec<float, 4> {
-    using type = float4;
+struct Vec {
+    typedef T type __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));
 };
 
-// Loads and stores of VEC consecutive elements in 16-byte (or narrower)
-// pieces; the address is aligned to min(16, VEC * sizeof(T)) bytes.
+// Loads and stores of VEC consecutive elements in pieces of up to 16 bytes.
 template <typename T, int VEC>
 __device__ __forceinline__ void load_vec(const T *p, T (&v)[VEC]) {
-    constexpr int C = 16 / (int)sizeof(T);
-    if constexpr (VEC > C) {
-        static_assert(VEC % C == 0, "vector width must be a multiple of 16 bytes");
+    constexpr int C = VEC * (int)sizeof(T) > 16 ? 16 / (int)sizeof(T) : VEC;
+    static_assert(VEC % C == 0, "vector width must be a multiple of 16 bytes");
 #pragma unroll
-        for (int k = 0; k < VEC / C; ++k) {
-            T t[C];
-            load_vec<T, C>(p + k * C, t);
-#pragma unroll
-            for (int j = 0; j < C; ++j) v[k * C + j] = t[j];
-        }
-    } else {
-        using V = typename Vec<T, VEC>::type;
-        V x = *reinterpret_cast<const V *>(p);
-        if constexpr (VEC == 1) {
-            v[0] = x;
-        } else if constexpr (VEC == 2) {
-            v[0] = x.x;
-            v[1] = x.y;
+    for (int k = 0; k < VEC / C; ++k) {
+        if constexpr (C == 1) {
+            v[k] = p[k];
         } else {
-            v[0] = x.x;
-            v[1] = x.y;
-            v[2] = x.z;
-            v[3] = x.w;
+            const auto x = *reinterpret_cast<const typename Vec<T, C>::type *>(p + k * C);
+#pragma unroll
+            for (int j = 0; j < C; ++j) v[k * C + j] = x[j];
         }
     }
 }
 
 template <typename T, int VEC>
 __device__ __forceinline__ void store_vec(T *p, const T (&v)[VEC]) {
-    constexpr int C = 16 / (int)sizeof(T);
-    if constexpr (VEC > C) {
-        static_assert(VEC % C == 0, "vector width must be a multiple of 16 bytes");
+    constexpr int C = VEC * (int)sizeof(T) > 16 ? 16 / (int)sizeof(T) : VEC;
+    static_assert(VEC % C == 0, "vector width must be a multiple of 16 bytes");
 #pragma unroll
-        for (int k = 0; k < VEC / C; ++k) {
-            T t[C];
-#pragma unroll
-            for (int j = 0; j < C; ++j) t[j] = v[k * C + j];
-            store_vec<T, C>(p + k * C, t);
-        }
-    } else {
-        using V = typename Vec<T, VEC>::type;
-        V x;
-        if constexpr (VEC == 1) {
-            x = v[0];
-        } else if constexpr (VEC == 2) {
-            x.x = v[0];
-            x.y = v[1];
+    for (int k = 0; k < VEC / C; ++k) {
+        if constexpr (C == 1) {
+            p[k] = v[k];
         } else {
-            x.x = v[0];
-            x.y = v[1];
-            x.z = v[2];
-            x.w = v[3];
+            typename Vec<T, C>::type x;
+#pragma unroll
+            for (int j = 0; j < C; ++j) x[j] = v[k * C + j];
+            *reinterpret_cast<typename Vec<T, C>::type *>(p + k * C) = x;
         }
-        *reinterpret_cast<V *>(p) = x;
     }
+}
+
+// store_vec of a lane's values as the output type.
+template <typename T, typename Tout, int VEC>
+__device__ __forceinline__ void store_cast(Tout *p, const T (&v)[VEC]) {
+    Tout o[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) o[i] = (Tout)v[i];
+    store_vec<Tout, VEC>(p, o);
 }
 
 }  // namespace

@@ -19,21 +19,47 @@ namespace flp {
 
 namespace {
 
-// LPR lanes share one matrix row; lane `sub` owns columns
-// [sub*VEC, sub*VEC + VEC) of the block.  All lanes of a row walk the row's
-// nonzeros together (the column index and value loads of a row coalesce to
-// one request), and each gathers its VEC contiguous entries of X[col, :].
+// A step's arguments as one kernel argument: the host's cost of a launch
+// grows with the number of arguments (one struct 2.8 us, 21 single ones 3.3,
+// and a step on a matrix of up to some tens of thousands of rows is bound by
+// that cost: 24^3 rows, r = 8 in FP32, 4.1 -> 3.5 us per step).
+template <typename T, typename Tout>
+struct ChebArgs {
+    const int32_t *rowptr, *colind;
+    const T *val, *X, *V, *Y;
+    Tout *out;
+    int n, r, ldx, ldv, ldy, ldo;
+    T alpha, beta, gamma, delta;
+    int chunk;                 // tile-to-XCD mapping (chunk_tile)
+    int halo, range, nranges;  // sliding window only
+};
+
+// LPR lanes share one matrix row; lane `sub` owns columns [c0, c0 + VEC) of
+// the block, c0 = sub * VEC, or the last VEC columns where that would run past
+// column r - 1: block widths that no shape covers exactly are read in whole
+// pieces by lanes that overlap (they compute and store the same values), so
+// no lane of a row is idle or loads single elements.  All lanes of a row walk
+// the row's nonzeros together, and each gathers its VEC contiguous entries of
+// X[col, :].  The step is bound by the number of gather requests in flight:
+// one element per lane against overlapping 16-byte pieces took 11.1 -> 5.8 us
+// (13 points, 37^3, r = 5, FP64), 33.6 -> 15.1 (60^3), 85.0 -> 39.5 (7 points,
+// 100^3, r = 5), 101.6 -> 47.3 (r = 6), 84.5 -> 38.4 (r = 12, FP32).
 // SELL: rowptr holds the slice offsets and colind / val the sliced ELL
 // arrays (sell_gather).
 // WIN: the block first stages the rows of X it and its neighbours within
 // kWinHalo rows use (stage_window) and gathers those from LDS; the shape
 // must then cover exactly the r = LPR * VEC columns in 16-byte pieces.
 template <typename T, typename Tout, int LPR, int VEC, bool NT, bool SELL, bool WIN>
-__global__ __launch_bounds__(256) void cheb_step_kernel(
-    int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colind,
-    const T *__restrict__ val, int r, const T *__restrict__ X, int ldx, const T *__restrict__ V,
-    int ldv, const T *__restrict__ Y, int ldy, Tout *__restrict__ out, int ldo, T alpha, T beta,
-    T gamma, T delta, int chunk) {
+__global__ __launch_bounds__(256) void cheb_step_kernel(const ChebArgs<T, Tout> p) {
+    const int n = p.n, r = p.r, ldx = p.ldx, ldv = p.ldv, ldy = p.ldy, ldo = p.ldo, chunk = p.chunk;
+    const int32_t *__restrict__ rowptr = p.rowptr;
+    const int32_t *__restrict__ colind = p.colind;
+    const T *__restrict__ val = p.val;
+    const T *__restrict__ X = p.X;
+    const T *__restrict__ V = p.V;
+    const T *__restrict__ Y = p.Y;
+    Tout *__restrict__ out = p.out;
+    const T alpha = p.alpha, beta = p.beta, gamma = p.gamma, delta = p.delta;
     constexpr int RPB = 256 / LPR;  // rows per block
     constexpr int GW = LPR * VEC;
     constexpr int WLD = GW + 16 / (int)sizeof(T);  // LDS row stride: 16 bytes of padding against bank conflicts
@@ -41,7 +67,7 @@ __global__ __launch_bounds__(256) void cheb_step_kernel(
     const int r0 = tile * RPB;
     const int row = r0 + threadIdx.x / LPR;
     const int sub = threadIdx.x % LPR;
-    const int c0 = sub * VEC;
+    const int c0 = min(sub * VEC, r - VEC);
     XSource<T, VEC, WIN> xs{X, ldx, c0, nullptr, 0, WLD, 0u};
     if constexpr (WIN) {
         __shared__ T win[(RPB + 2 * kWinHalo) * WLD];
@@ -53,11 +79,11 @@ __global__ __launch_bounds__(256) void cheb_step_kernel(
         xs.wlo = wlo;
         xs.wlen = (unsigned)(whi - wlo);
     }
-    if (row >= n || c0 >= r) return;
+    if (row >= n || (VEC == 1 && sub >= r)) return;
     T acc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = T(0);
-    if constexpr (VEC > 1) {  // the aligned shapes: LPR * VEC = r, every lane of a row active
+    if constexpr (VEC > 1) {  // every lane of a row active
         gather_row<T, VEC, LPR, SELL, WIN>(row, sub, rowptr, colind, val, xs, acc);
     } else if constexpr (SELL) {
         const int sl = row / kSellC;
@@ -72,7 +98,7 @@ __global__ __launch_bounds__(256) void cheb_step_kernel(
     xs.load(row, xr);
     T res[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) res[v] = alpha * acc[v] + beta * xr[v];
+    for (int v = 0; v < VEC; ++v) res[v] = fma(alpha, acc[v], beta * xr[v]);
     if (V) {
         T vv[VEC];
         load_stream<T, VEC, NT>(V + (int64_t)row * ldv + c0, vv);
@@ -85,31 +111,17 @@ __global__ __launch_bounds__(256) void cheb_step_kernel(
 #pragma unroll
         for (int v = 0; v < VEC; ++v) res[v] = fma(delta, yy[v], res[v]);
     }
-    if constexpr (sizeof(Tout) == sizeof(T)) {
-        store_vec<Tout, VEC>(out + (int64_t)row * ldo + c0, res);
-    } else {
-        Tout o[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) o[v] = (Tout)res[v];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) out[(int64_t)row * ldo + c0 + v] = o[v];
-    }
+    store_cast<T, Tout, VEC>(out + (int64_t)row * ldo + c0, res);
 }
 
 template <typename T, typename Tout, int LPR, int VEC, bool NT, bool WIN>
-hipError_t cheb_launch(int n, const int32_t *rowptr, const int32_t *colind, const T *val, int r,
-                       const T *X, int ldx, const T *V, int ldv, const T *Y, int ldy, Tout *out,
-                       int ldo, T alpha, T beta, T gamma, T delta, hipStream_t s, bool sell, int chunk) {
+hipError_t cheb_launch(const ChebArgs<T, Tout> &p, hipStream_t s, bool sell) {
     constexpr int RPB = 256 / LPR;
-    int grid = (n + RPB - 1) / RPB;
+    const dim3 grid((p.n + RPB - 1) / RPB);
     if (sell)
-        hipLaunchKernelGGL((cheb_step_kernel<T, Tout, LPR, VEC, NT, true, WIN>), dim3(grid), dim3(256), 0, s, n,
-                           rowptr, colind, val, r, X, ldx, V, ldv, Y, ldy, out, ldo, alpha, beta, gamma, delta,
-                           chunk);
+        hipLaunchKernelGGL((cheb_step_kernel<T, Tout, LPR, VEC, NT, true, WIN>), grid, dim3(256), 0, s, p);
     else
-        hipLaunchKernelGGL((cheb_step_kernel<T, Tout, LPR, VEC, NT, false, WIN>), dim3(grid), dim3(256), 0, s, n,
-                           rowptr, colind, val, r, X, ldx, V, ldv, Y, ldy, out, ldo, alpha, beta, gamma, delta,
-                           chunk);
+        hipLaunchKernelGGL((cheb_step_kernel<T, Tout, LPR, VEC, NT, false, WIN>), grid, dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
@@ -126,11 +138,17 @@ hipError_t cheb_launch(int n, const int32_t *rowptr, const int32_t *colind, cons
 // workgroups k +- m (on the same XCD, xcd_tile) load at the same time.
 // Same sums as cheb_step_kernel.
 template <typename T, typename Tout, int LPR, int VEC, bool NT, bool SELL>
-__global__ __launch_bounds__(256) void cheb_slide_kernel(
-    int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colind,
-    const T *__restrict__ val, int r, const T *__restrict__ X, int ldx, const T *__restrict__ V,
-    int ldv, const T *__restrict__ Y, int ldy, Tout *__restrict__ out, int ldo, T alpha, T beta,
-    T gamma, T delta, int halo, int range, int nranges) {
+__global__ __launch_bounds__(256) void cheb_slide_kernel(const ChebArgs<T, Tout> p) {
+    const int n = p.n, r = p.r, ldx = p.ldx, ldv = p.ldv, ldy = p.ldy, ldo = p.ldo;
+    const int halo = p.halo, range = p.range, nranges = p.nranges;
+    const int32_t *__restrict__ rowptr = p.rowptr;
+    const int32_t *__restrict__ colind = p.colind;
+    const T *__restrict__ val = p.val;
+    const T *__restrict__ X = p.X;
+    const T *__restrict__ V = p.V;
+    const T *__restrict__ Y = p.Y;
+    Tout *__restrict__ out = p.out;
+    const T alpha = p.alpha, beta = p.beta, gamma = p.gamma, delta = p.delta;
     constexpr int RPB = 256 / LPR;
     constexpr int GW = LPR * VEC;
     constexpr int WLD = GW + 16 / (int)sizeof(T);
@@ -183,7 +201,7 @@ __global__ __launch_bounds__(256) void cheb_slide_kernel(
             xs.load(row, xr);
             T res[VEC];
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) res[v] = alpha * acc[v] + beta * xr[v];
+            for (int v = 0; v < VEC; ++v) res[v] = fma(alpha, acc[v], beta * xr[v]);
             if (V) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) res[v] = fma(gamma, vv[v], res[v]);
@@ -192,12 +210,7 @@ __global__ __launch_bounds__(256) void cheb_slide_kernel(
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) res[v] = fma(delta, yy[v], res[v]);
             }
-            if constexpr (sizeof(Tout) == sizeof(T)) {
-                store_vec<Tout, VEC>(out + (int64_t)row * ldo + c0, res);
-            } else {
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) out[(int64_t)row * ldo + c0 + v] = (Tout)res[v];
-            }
+            store_cast<T, Tout, VEC>(out + (int64_t)row * ldo + c0, res);
         }
         __syncthreads();  // every read of this window is done
         if (more) {
@@ -263,9 +276,7 @@ int slide_range(int n, int plane, int slots, int rpb) {
 }
 
 template <typename T, typename Tout, int LPR, int VEC, bool NT>
-hipError_t slide_launch(int n, const int32_t *rowptr, const int32_t *colind, const T *val, int r, const T *X,
-                        int ldx, const T *V, int ldv, const T *Y, int ldy, Tout *out, int ldo, T alpha, T beta,
-                        T gamma, T delta, hipStream_t s, bool sell, int halo, int plane) {
+hipError_t slide_launch(ChebArgs<T, Tout> p, hipStream_t s, bool sell, int halo, int plane) {
     constexpr int RPB = 256 / LPR;
     constexpr int WLD = LPR * VEC + 16 / (int)sizeof(T);
     if (halo < 0 || halo > (1 << 16)) return hipErrorInvalidValue;
@@ -274,10 +285,10 @@ hipError_t slide_launch(int n, const int32_t *rowptr, const int32_t *colind, con
     int slots = 0;
     hipError_t e = slide_slots((const void *)kfn, lds, &slots);
     if (e != hipSuccess) return e;
-    const int range = slide_range(n, plane, slots, RPB);
-    const int nr = (int)(((int64_t)n + range - 1) / range);
-    hipLaunchKernelGGL(kfn, dim3(nr), dim3(256), lds, s, n, rowptr, colind, val, r, X, ldx, V, ldv, Y, ldy, out,
-                       ldo, alpha, beta, gamma, delta, halo, range, nr);
+    p.halo = halo;
+    p.range = slide_range(p.n, plane, slots, RPB);
+    p.nranges = (int)(((int64_t)p.n + p.range - 1) / p.range);
+    hipLaunchKernelGGL(kfn, dim3(p.nranges), dim3(256), lds, s, p);
     return hipGetLastError();
 }
 
@@ -307,11 +318,11 @@ __global__ __launch_bounds__(256) void sell_fill_kernel(int n, int nslots, const
 
 }  // namespace
 
-// Aligned launch shapes (LPR lanes per row x VEC columns per lane) with a
-// kernel instance: FP64 in 16-, 32- and 64-byte pieces per lane, FP32 in 16-
-// and 32-byte pieces.
+// Launch shapes (LPR lanes per row x VEC columns per lane) with a kernel
+// instance: FP64 in 16-, 32- and 64-byte pieces per lane, FP32 in 16- and
+// 32-byte pieces (8-byte ones for 2 and 3 columns).
 #define FLP_SHAPES_F64(X) X(1, 2) X(2, 2) X(4, 2) X(8, 2) X(16, 2) X(1, 4) X(2, 4) X(4, 4) X(8, 4) X(1, 8) X(2, 8) X(4, 8)
-#define FLP_SHAPES_F32(X) X(1, 4) X(2, 4) X(4, 4) X(8, 4) X(1, 8) X(2, 8) X(4, 8)
+#define FLP_SHAPES_F32(X) X(1, 2) X(2, 2) X(1, 4) X(2, 4) X(4, 4) X(8, 4) X(1, 8) X(2, 8) X(4, 8)
 
 static bool shape_has_kernel(bool fp32, int lpr, int vec) {
 #define FLP_HAS(L, V) if (lpr == L && vec == V) return true;
@@ -330,18 +341,32 @@ StepShape default_step_shape(int r, bool fp32) {
     return StepShape{0, 0};
 }
 
+// Lanes for r columns in pieces of vec: r / vec where that is a power of
+// two, else the next one, whose last lanes overlap (cheb_step_kernel).
+static int lanes_for(int r, int vec) {
+    int l = 1;
+    while (l * vec < r) l *= 2;
+    return l;
+}
+
 std::vector<StepShape> step_shape_candidates(int r, bool fp32, bool window) {
     std::vector<StepShape> out;
     for (int win = 0; win <= (window ? 1 : 0); ++win)
         for (int nt : {0, 1})
-            for (int vec : {2, 4, 8})
-                if (r % vec == 0 && shape_has_kernel(fp32, r / vec, vec))
-                    out.push_back(StepShape{r / vec, vec, nt, 0, win});
+            for (int vec : {2, 4, 8}) {
+                const StepShape sh{vec <= r ? lanes_for(r, vec) : 0, vec, nt, 0, win};
+                // the window stages whole 16-byte pieces of exactly r columns
+                if (step_shape_ok(r, fp32, sh) && (win == 0 || step_shape_exact(r, fp32, sh))) out.push_back(sh);
+            }
     return out;
 }
 
 bool step_shape_ok(int r, bool fp32, StepShape sh) {
-    return sh.lpr > 0 && sh.lpr * sh.vec == r && shape_has_kernel(fp32, sh.lpr, sh.vec);
+    return sh.lpr > 0 && sh.vec <= r && sh.lpr == lanes_for(r, sh.vec) && shape_has_kernel(fp32, sh.lpr, sh.vec);
+}
+
+bool step_shape_exact(int r, bool fp32, StepShape sh) {
+    return sh.lpr * sh.vec == r && sh.vec % (fp32 ? 4 : 2) == 0;
 }
 
 // One lane per column on the next power of two >= r lanes: the shape for
@@ -366,40 +391,48 @@ hipError_t launch_cheb_step(int n, const int32_t *rowptr, const int32_t *colind,
                             int ldo, T alpha, T beta, T gamma, T delta, hipStream_t s, StepShape sh, bool sell) {
     if (n <= 0) return hipSuccess;
     constexpr bool F32 = sizeof(T) == 4;
-    // vector loads need every leading dimension and base aligned to 16 bytes
-    constexpr int V16 = 16 / (int)sizeof(T);
-    auto al = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    bool aligned16 = (ldx % V16 == 0) && (!V || ldv % V16 == 0) && (!Y || ldy % V16 == 0) &&
-                     (ldo % V16 == 0) && (sizeof(Tout) == sizeof(T)) && al(X) && al(V) && al(Y) && al(out);
-#define FLP_CHEB_NW(LPR, VEC, NT, WIN) \
-    return cheb_launch<T, Tout, LPR, VEC, NT, WIN>(n, rowptr, colind, val, r, X, ldx, V, ldv, Y, ldy, out, ldo, alpha, beta, gamma, delta, s, sell, sh.chunk)
-#define FLP_CHEB(LPR, VEC) FLP_CHEB_NW(LPR, VEC, false, false)
-    if (aligned16 && r % V16 == 0) {
-        if (!step_shape_ok(r, F32, sh)) {
-            const int chunk = sh.chunk;
-            sh = default_step_shape(r, F32);
-            sh.chunk = chunk;
-        }
-        const int lpr = sh.lpr, vec = sh.vec;
-        const bool nt = sh.nt != 0, win = sh.win == 1, slide = sh.win == 2;
-#define FLP_TRY(L, VV)                           \
-    if (lpr == L && vec == VV) {                 \
-        if (slide) {                             \
-            if (nt)                              \
-                return slide_launch<T, Tout, L, VV, true>(n, rowptr, colind, val, r, X, ldx, V, ldv, Y, ldy, out, ldo, alpha, beta, gamma, delta, s, sell, sh.halo, sh.chunk); \
-            return slide_launch<T, Tout, L, VV, false>(n, rowptr, colind, val, r, X, ldx, V, ldv, Y, ldy, out, ldo, alpha, beta, gamma, delta, s, sell, sh.halo, sh.chunk); \
-        }                                        \
-        if (win) {                               \
-            if (nt) {                            \
-                FLP_CHEB_NW(L, VV, true, true);  \
-            } else {                             \
-                FLP_CHEB_NW(L, VV, false, true); \
-            }                                    \
-        } else if (nt) {                         \
-            FLP_CHEB_NW(L, VV, true, false);     \
-        } else {                                 \
-            FLP_CHEB_NW(L, VV, false, false);    \
-        }                                        \
+    ChebArgs<T, Tout> p{};
+    p.rowptr = rowptr;
+    p.colind = colind;
+    p.val = val;
+    p.X = X;
+    p.V = V;
+    p.Y = Y;
+    p.out = out;
+    p.n = n;
+    p.r = r;
+    p.ldx = ldx;
+    p.ldv = ldv;
+    p.ldy = ldy;
+    p.ldo = ldo;
+    p.alpha = alpha;
+    p.beta = beta;
+    p.gamma = gamma;
+    p.delta = delta;
+    p.chunk = sh.chunk;
+    if (!step_shape_ok(r, F32, sh)) {
+        const int chunk = sh.chunk;
+        sh = default_step_shape(r, F32);
+        sh.chunk = chunk;
+    }
+    if (sh.lpr > 0) {
+        // the LDS windows are staged in aligned 16-byte pieces of exactly r
+        // columns; other blocks run the same shape without one
+        const bool staged = step_shape_exact(r, F32, sh) && ldx % (16 / (int)sizeof(T)) == 0 &&
+                            (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+        const bool nt = sh.nt != 0, win = staged && sh.win == 1, slide = staged && sh.win == 2;
+#define FLP_TRY(L, VV)                                                                                       \
+    if (sh.lpr == L && sh.vec == VV) {                                                                       \
+        if constexpr (VV * sizeof(T) % 16 == 0) {                                                            \
+            if (slide)                                                                                       \
+                return nt ? slide_launch<T, Tout, L, VV, true>(p, s, sell, sh.halo, sh.chunk)                 \
+                          : slide_launch<T, Tout, L, VV, false>(p, s, sell, sh.halo, sh.chunk);               \
+            if (win)                                                                                         \
+                return nt ? cheb_launch<T, Tout, L, VV, true, true>(p, s, sell)                               \
+                          : cheb_launch<T, Tout, L, VV, false, true>(p, s, sell);                             \
+        }                                                                                                    \
+        return nt ? cheb_launch<T, Tout, L, VV, true, false>(p, s, sell)                                      \
+                  : cheb_launch<T, Tout, L, VV, false, false>(p, s, sell);                                    \
     }
         if constexpr (F32) {
             FLP_SHAPES_F32(FLP_TRY)
@@ -408,14 +441,14 @@ hipError_t launch_cheb_step(int n, const int32_t *rowptr, const int32_t *colind,
         }
 #undef FLP_TRY
     }
-    if (r == 1) FLP_CHEB(1, 1);
-    if (r == 2) FLP_CHEB(2, 1);
-    if (r <= 4) FLP_CHEB(4, 1);
-    if (r <= 8) FLP_CHEB(8, 1);
-    if (r <= 16) FLP_CHEB(16, 1);
-    if (r <= 32) FLP_CHEB(32, 1);
+#define FLP_CHEB(LPR) return cheb_launch<T, Tout, LPR, 1, false, false>(p, s, sell)
+    if (r == 1) FLP_CHEB(1);
+    if (r == 2) FLP_CHEB(2);
+    if (r <= 4) FLP_CHEB(4);
+    if (r <= 8) FLP_CHEB(8);
+    if (r <= 16) FLP_CHEB(16);
+    if (r <= 32) FLP_CHEB(32);
 #undef FLP_CHEB
-#undef FLP_CHEB_NW
     return hipErrorInvalidValue;
 }
 
@@ -456,9 +489,8 @@ hipError_t launch_sell_fill(int n, const int32_t *rowptr, const int32_t *colind,
 
 namespace {
 
-// Lane `sub` of a row owns columns [sub*VEC, sub*VEC + VEC); when LPR * VEC
-// exceeds the block width r (the one-column-per-lane shapes for r that is
-// not a power of two), lanes past column r - 1 have no column and leave.
+// The lanes' columns as in cheb_step_kernel.  (VEC = 1 is the untuned shape
+// for widths with no exact one: the lanes past column r - 1 leave.)
 template <typename T, int LPR, int VEC, bool NT, bool WIN>
 __global__ __launch_bounds__(256) void cheb_seg_kernel(const SegEntry *__restrict__ tab, int nseg, int r,
                                                        int chunk) {
@@ -485,7 +517,7 @@ __global__ __launch_bounds__(256) void cheb_seg_kernel(const SegEntry *__restric
     const int r0 = (tile - e.tile0) * RPB;
     const int row = r0 + threadIdx.x / LPR;
     const int sub = threadIdx.x % LPR;
-    const int c0 = sub * VEC;
+    const int c0 = min(sub * VEC, r - VEC);
     const T *__restrict__ X = (const T *)e.X;
     const int ldx = e.ldx;
     XSource<T, VEC, WIN> xs{X, ldx, c0, nullptr, 0, WLD, 0u};
@@ -499,14 +531,14 @@ __global__ __launch_bounds__(256) void cheb_seg_kernel(const SegEntry *__restric
         xs.wlo = wlo;
         xs.wlen = (unsigned)(whi - wlo);
     }
-    if (row >= n || c0 >= r) return;
+    if (row >= n || (VEC == 1 && sub >= r)) return;
     const int32_t *__restrict__ rowptr = e.rowptr;
     const int32_t *__restrict__ colind = e.colind;
     const T *__restrict__ val = (const T *)e.val;
     T acc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = T(0);
-    if constexpr (VEC > 1) {  // aligned shapes: LPR * VEC = r
+    if constexpr (VEC > 1) {  // every lane of a row active
         if (e.sell)
             gather_row<T, VEC, LPR, true, WIN>(row, sub, rowptr, colind, val, xs, acc);
         else
@@ -525,7 +557,7 @@ __global__ __launch_bounds__(256) void cheb_seg_kernel(const SegEntry *__restric
     const T alpha = (T)e.alpha, beta = (T)e.beta, gamma = (T)e.gamma, delta = (T)e.delta;
     T res[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) res[v] = alpha * acc[v] + beta * xr[v];
+    for (int v = 0; v < VEC; ++v) res[v] = fma(alpha, acc[v], beta * xr[v]);
     if (e.V) {
         T vv[VEC];
         load_stream<T, VEC, NT>((const T *)e.V + (int64_t)row * e.ldv + c0, vv);
@@ -539,9 +571,7 @@ __global__ __launch_bounds__(256) void cheb_seg_kernel(const SegEntry *__restric
         for (int v = 0; v < VEC; ++v) res[v] = fma(delta, yy[v], res[v]);
     }
     if (e.out_f64) {
-        double *o = (double *)e.out + (int64_t)row * e.ldo + c0;
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) o[v] = (double)res[v];
+        store_cast<T, double, VEC>((double *)e.out + (int64_t)row * e.ldo + c0, res);
     } else {
         store_vec<T, VEC>((T *)e.out + (int64_t)row * e.ldo + c0, res);
     }
@@ -582,19 +612,22 @@ hipError_t launch_cheb_seg(bool fp32, int r, const SegEntry *tab, int nseg, int 
 #define FLP_SEG(T, LPR, VEC) FLP_SEG_NW(T, LPR, VEC, false, false)
 #define FLP_SEGT(T, L, VV) \
     if (lpr == L && vec == VV) { \
-        if (win) { \
-            if (nt) \
-                FLP_SEG_NW(T, L, VV, true, true) \
-            else \
-                FLP_SEG_NW(T, L, VV, false, true) \
-        } else if (nt) \
+        if constexpr (VV * sizeof(T) % 16 == 0) { \
+            if (win) { \
+                if (nt) \
+                    FLP_SEG_NW(T, L, VV, true, true) \
+                else \
+                    FLP_SEG_NW(T, L, VV, false, true) \
+            } \
+        } \
+        if (nt) \
             FLP_SEG_NW(T, L, VV, true, false) \
         else \
             FLP_SEG_NW(T, L, VV, false, false) \
     }
 #define FLP_SEG64(L, VV) FLP_SEGT(double, L, VV)
 #define FLP_SEG32(L, VV) FLP_SEGT(float, L, VV)
-    const bool win = sh.win != 0;
+    const bool win = sh.win != 0 && step_shape_exact(r, fp32, sh);
     if (!fp32) {
         FLP_SHAPES_F64(FLP_SEG64)
         if (vec == 1) {

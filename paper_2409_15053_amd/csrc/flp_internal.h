@@ -79,8 +79,9 @@ inline DMat panel_mat(const double *p, int64_t n, int lpw) {
 // All take a stream and return hipError_t from the launch.
 
 // Launch shape of a filter step: lpr lanes share one matrix row and each
-// owns vec consecutive columns of the block (lpr * vec = r), so a 256-thread
-// block covers 256 / lpr rows; nt = 1 reads the streamed operands (V and
+// owns vec consecutive columns of the block (lpr * vec = r, or lpr the next
+// power of two, its last lanes overlapping), so a 256-thread block covers
+// 256 / lpr rows; nt = 1 reads the streamed operands (V and
 // U_{k+2}) with nontemporal loads.  {0, 0, 0} selects the default (16-byte
 // pieces, ordinary loads).  chunk: the tile-to-XCD mapping (chunk_tile in
 // flp_device.h; 0 = one contiguous range per XCD).  Every shape sums each
@@ -105,6 +106,8 @@ StepShape default_step_shape(int r, bool fp32);
 // window: also the LDS-window variants (single-solve kernel only)
 std::vector<StepShape> step_shape_candidates(int r, bool fp32, bool window);
 bool step_shape_ok(int r, bool fp32, StepShape sh);
+// lpr * vec = r in 16-byte pieces: the shapes that have the LDS windows
+bool step_shape_exact(int r, bool fp32, StepShape sh);
 
 // out = alpha * (A X) + beta * X + gamma * V + delta * Y, row-major blocks of
 // r columns with leading dimensions; V / Y may be NULL (their terms skipped).

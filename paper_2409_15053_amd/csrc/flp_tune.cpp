@@ -146,6 +146,17 @@ int plane_of(const std::vector<int> &offs) {
 
 }  // namespace
 
+// Walking planes and sliding windows pay where the gathered block falls out
+// of the caches between planes.  Measured without / with them, us per step:
+// 16 MB per step (37^3, 13 points, r = 5) 5.84 / 6.42, 20 MB (48^3, r = 8,
+// FP32) 5.17 / 5.25, 38 MB (48^3, FP64) 7.21 / 7.42, 68 MB (60^3, 13 points,
+// r = 5) 15.9 / 15.1.  Below 32 MB they are not tried: finding them reads a
+// row of the matrix, two host round trips (about 45 us) on every call, more
+// than six steps of such a filter.
+static bool plane_pays(const flp_csr *A, int r, bool fp32) {
+    return filter_step_bytes(A->n, A->nnz, r, fp32 ? FLP_PREC_FP32_FILTER : FLP_PREC_FP64) > 32e6;
+}
+
 int plane_rows(const flp_csr *A, bool sell, hipStream_t s, int *out) {
     std::vector<int> offs;
     CKR(row_offsets(A, sell, s, &offs));
@@ -178,7 +189,7 @@ int lookup_filter_tune(const flp_csr *A, int r, bool fp32, FilterTune *out) {
     CK(hipGetDevice(&dev));
     const int n = A->n;
     int plane = 0;
-    CKR(plane_rows(A, false, nullptr, &plane));
+    if (plane_pays(A, r, fp32)) CKR(plane_rows(A, false, nullptr, &plane));
     const int64_t nc = std::lround(4.0 * std::log2((double)n)), zc = std::lround(4.0 * (double)A->nnz / n);
     // a single solve's tuning (either storage) first, then the segmented engine's
     const Key keys[] = {Key{dev, fp32 ? 1 : 0, r, nc, zc, 1, 1, plane}, Key{dev, fp32 ? 1 : 0, r, nc, zc, 1, 0, plane},
@@ -207,6 +218,7 @@ int tune_filter(const flp_csr *A, const float *val32, int r, bool fp32, bool all
             if (g_force_gw > 0 && r % g_force_gw == 0 && (allow_groups || g_force_gw == r)) f.gw = g_force_gw;
             if (step_shape_ok(f.gw, fp32, g_force_shape)) {
                 f.sh = g_force_shape;
+                if (!step_shape_exact(f.gw, fp32, f.sh)) f.sh.win = 0;
                 if (f.sh.win == 2 && f.sh.halo == 0) {  // sliding window fitted to this matrix
                     std::vector<int> offs;
                     CKR(row_offsets(A, sell, s, &offs));
@@ -237,7 +249,7 @@ int tune_filter(const flp_csr *A, const float *val32, int r, bool fp32, bool all
     // a single solve's filter also tries the pencil walk over the matrix's
     // planes (the segmented engine's tiles span many matrices)
     std::vector<int> offs;
-    if (allow_groups) CKR(row_offsets(A, sell, s, &offs));
+    if (allow_groups && plane_pays(A, r, fp32)) CKR(row_offsets(A, sell, s, &offs));
     const int plane = plane_of(offs);
     // size class: n to a quarter octave, nonzeros per row to a quarter; plane
     const Key key{dev, fp32 ? 1 : 0, r, (int64_t)std::lround(4.0 * std::log2((double)n)),
@@ -280,13 +292,15 @@ int tune_filter(const flp_csr *A, const float *val32, int r, bool fp32, bool all
             }
         }
         // the sliding window, its halo and row ranges fitted to the matrix
-        for (StepShape sh : step_shape_candidates(gw, fp32, false))
+        for (StepShape sh : step_shape_candidates(gw, fp32, false)) {
+            if (!step_shape_exact(gw, fp32, sh)) continue;
             for (int h : slide_halos(offs, plane, gw, sh.lpr, es)) {
                 sh.halo = h;
                 sh.win = 2;
                 sh.chunk = plane;
                 cands.push_back(sh);
             }
+        }
         for (StepShape sh : cands) {
             // V: the caller's block (gw == r) or a contiguous n x gw group,
             // taken from the unused half of the first buffer
