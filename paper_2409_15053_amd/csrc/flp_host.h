@@ -372,7 +372,7 @@ struct Solve {
     double *pin = nullptr;
     double *gdev = nullptr;
     int checked_step = -1;  // block step whose convergence check was started
-    EigLog eig;             // rotation log of the deciding check's T_k
+    EigLog eig;             // orthogonal factors of the deciding check's T_k
     std::shared_ptr<CheckTask> check;  // check in flight (its T_k may be behind the current step)
     bool check_last = false;           // that check is the final one (no basis room left)
     double t_step0 = 0.0;   // host time the current block step started

@@ -31,28 +31,29 @@ void set_error(const std::string &msg);
 int sym_eig(int N, int bw, const double *M, double *evals, const int *rows, int nrows, double *Zrows,
             const int *cols = nullptr, int ncols = 0, double *Zcols = nullptr);
 
-// The rotation log of one sym_eig call, kept so eigenvector columns can be
-// produced later without repeating the reduction.
-struct EigRot {
-    int32_t p;  // plane (p, p+1)
-    double c, s;
-};
+// The orthogonal factors of one sym_eig call, kept so eigenvector columns can
+// be produced later without repeating the reduction: the reflectors of the
+// band reduction in the order made (I - beta v v^T on the b rows from row,
+// fewer at the end of the matrix; v(0) = 1), then the QR sweeps, each a run
+// of rotations on the planes (lo, lo + 1) .. (lo + len - 1, lo + len).
 struct EigLog {
-    int N = 0;
-    std::vector<EigRot> rot;
+    struct Sweep {
+        int32_t lo, len;
+        size_t at;  // first of the len (c, s) pairs in cs
+    };
+    int N = 0, b = 0;
+    std::vector<int32_t> row;  // reflectors
+    std::vector<double> beta, v;
+    std::vector<Sweep> sweep;
+    std::vector<double> cs;
     std::vector<int> perm;  // sorted position -> unsorted index
-    void clear() {
-        N = 0;
-        rot.clear();
-        rot.shrink_to_fit();
-        perm.clear();
-    }
+    void clear() { *this = EigLog(); }
 };
 // Caps the threads one eigensolver call started from the calling thread may
 // use (default 16).
 void set_eig_threads(int n);
 
-// sym_eig that also returns its rotation log in *keep
+// sym_eig that also returns its factors in *keep
 int sym_eig_keep(int N, int bw, const double *M, double *evals, const int *rows, int nrows, double *Zrows,
                  EigLog *keep);
 // columns cols[0..ncols) (sorted order) of the eigenvector matrix of a kept

@@ -472,7 +472,7 @@ int solve_finish(Solve &S, flp_result **out) {
     if (c > 0) {
         const int K = S.kfinal;
         // eigenvectors of T_k for the candidates (eq. proj) and guards, from
-        // the rotation log the last convergence check kept
+        // the factors the last convergence check kept
         std::vector<double> Zc((size_t)K * c);
         const double tc = now();
         if (S.eig.N != K) return fail(FLP_E_DEVICE, "internal: no eigen-decomposition of the final T_k");
