@@ -190,8 +190,7 @@ void flp_set_filter_shape(int32_t lanes_per_row, int32_t cols_per_lane, int32_t 
 int flp_spmm(const flp_csr *A, const double *X, int32_t ldx, double *Y, int32_t ldy, int32_t r, void *stream) {
     CKR(check_csr(A));
     if (r < 1 || r > 32 || ldx < r || ldy < r || !X || !Y) return fail(FLP_E_ARG, "bad block arguments");
-    CK(launch_cheb_step<double, double>(A->n, A->rowptr, A->colind, A->val, r, X, ldx, nullptr, 0, nullptr, 0, Y,
-                                        ldy, 1.0, 0.0, 0.0, 0.0, (hipStream_t)stream));
+    CK(launch_product(A->n, A->rowptr, A->colind, A->val, r, X, ldx, Y, ldy, 0, (hipStream_t)stream));
     return FLP_OK;
 }
 

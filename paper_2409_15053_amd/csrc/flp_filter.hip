@@ -362,7 +362,7 @@ std::vector<StepShape> step_shape_candidates(int r, bool fp32, bool window) {
 }
 
 bool step_shape_ok(int r, bool fp32, StepShape sh) {
-    return sh.lpr > 0 && sh.vec <= r && sh.lpr == lanes_for(r, sh.vec) && shape_has_kernel(fp32, sh.lpr, sh.vec);
+    return shape_has_kernel(fp32, sh.lpr, sh.vec) && sh.vec <= r && sh.lpr == lanes_for(r, sh.vec);
 }
 
 bool step_shape_exact(int r, bool fp32, StepShape sh) {
@@ -464,6 +464,18 @@ template hipError_t launch_cheb_step<float, double>(int, const int32_t *, const 
                                                     const float *, int, const float *, int, const float *, int,
                                                     double *, int, float, float, float, float, hipStream_t,
                                                     StepShape, bool);
+
+// A product has no tuned shape of its own.  Pairs of columns per lane, the
+// last lanes overlapping, and the filter's plane walk where it took one:
+// 13 points, 60^3, us per product of r = 32 columns 65 -> 52 with the planes
+// (4 columns per lane 60), of 27 columns 123 (one per lane) -> 46, of 14
+// 62 -> 27; 7 points, 100^3, r = 32 245 -> 229, r = 6 100 -> 48.
+hipError_t launch_product(int n, const int32_t *rowptr, const int32_t *colind, const double *val, int r,
+                          const double *X, int ldx, double *Y, int ldy, int plane_chunk, hipStream_t s) {
+    const StepShape sh{lanes_for(r, 2), 2, 0, std::min(plane_chunk, 0)};  // (r = 1: one lane, one column)
+    return launch_cheb_step<double, double>(n, rowptr, colind, val, r, X, ldx, nullptr, 0, nullptr, 0, Y, ldy, 1.0,
+                                            0.0, 0.0, 0.0, s, sh);
+}
 
 void tile_order_host(int tiles, int chunk, int rows_per_tile, int32_t *order) {
     for (int b = 0; b < tiles; ++b) order[b] = chunk_tile(b, tiles, chunk, rows_per_tile);

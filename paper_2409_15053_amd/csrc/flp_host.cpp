@@ -1142,12 +1142,11 @@ int orthonormalize_cols(int n, int c, double *&Y, double *&tmp, int ldc, double 
 // G = Y^T A Y = Z diag(lam) Z^T, X = Y Z, AX = (A Y) Z and the residual
 // norms ||A x_j - lam_j x_j|| (host, unscaled).  lam ascending.
 int rayleigh_ritz(const flp_csr *A, int n, int c, const double *Y, double *AY, double *X, double *AX, int ldc,
-                  double *sdev, std::vector<double> &lam, std::vector<double> &res, hipStream_t s) {
+                  double *sdev, std::vector<double> &lam, std::vector<double> &res, int plane_chunk, hipStream_t s) {
     Workspace &w = ws();
     for (int j0 = 0; j0 < c; j0 += 32) {
         int cw = std::min(32, c - j0);
-        CK(launch_cheb_step<double, double>(n, A->rowptr, A->colind, A->val, cw, Y + j0, ldc, nullptr, 0, nullptr,
-                                            0, AY + j0, ldc, 1.0, 0.0, 0.0, 0.0, s));
+        CK(launch_product(n, A->rowptr, A->colind, A->val, cw, Y + j0, ldc, AY + j0, ldc, plane_chunk, s));
     }
     std::vector<double> G((size_t)c * c);
     CKR(gram_tn(n, c, c, plain_mat(Y, ldc), AY, ldc, sdev, G.data(), s, true));
@@ -1214,12 +1213,11 @@ void rows_parallel(int n, double work, F f) {
 }  // namespace
 
 int rayleigh_ritz_gen(const flp_csr *A, int n, int c, const double *Y, double *AY, double *X, double *AX, int ldc,
-                      double *sdev, std::vector<double> &lam, std::vector<double> &res, hipStream_t s) {
+                      double *sdev, std::vector<double> &lam, std::vector<double> &res, int plane_chunk, hipStream_t s) {
     Workspace &w = ws();
     for (int j0 = 0; j0 < c; j0 += 32) {
         int cw = std::min(32, c - j0);
-        CK(launch_cheb_step<double, double>(n, A->rowptr, A->colind, A->val, cw, Y + j0, ldc, nullptr, 0, nullptr,
-                                            0, AY + j0, ldc, 1.0, 0.0, 0.0, 0.0, s));
+        CK(launch_product(n, A->rowptr, A->colind, A->val, cw, Y + j0, ldc, AY + j0, ldc, plane_chunk, s));
     }
     std::vector<double> M((size_t)c * c), G((size_t)c * c);
     CKR(gram_tn(n, c, c, plain_mat(Y, ldc), Y, ldc, sdev, M.data(), s, true));
@@ -1279,8 +1277,7 @@ int rayleigh_ritz_gen(const flp_csr *A, int n, int c, const double *Y, double *A
     // rather than AY C (a dense n x c x c product on the FP64 matrix cores)
     for (int j0 = 0; j0 < c; j0 += 32) {
         int cw = std::min(32, c - j0);
-        CK(launch_cheb_step<double, double>(n, A->rowptr, A->colind, A->val, cw, X + j0, ldc, nullptr, 0, nullptr,
-                                            0, AX + j0, ldc, 1.0, 0.0, 0.0, 0.0, s));
+        CK(launch_product(n, A->rowptr, A->colind, A->val, cw, X + j0, ldc, AX + j0, ldc, plane_chunk, s));
     }
     double *lamd = sdev + (size_t)c * ldc;
     double *rdev = lamd + ldc;

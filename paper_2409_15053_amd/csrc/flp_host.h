@@ -282,9 +282,9 @@ int orthonormalize_cols(int n, int c, double *&Y, double *&tmp, int ldc, double 
 // The same for a block Y whose columns need not be orthonormal (Y itself is
 // left as it is): replaces orthonormalising Y and then rayleigh_ritz.
 int rayleigh_ritz_gen(const flp_csr *A, int n, int c, const double *Y, double *AY, double *X, double *AX, int ldc,
-                      double *sdev, std::vector<double> &lam, std::vector<double> &res, hipStream_t s);
+                      double *sdev, std::vector<double> &lam, std::vector<double> &res, int plane_chunk, hipStream_t s);
 int rayleigh_ritz(const flp_csr *A, int n, int c, const double *Y, double *AY, double *X, double *AX, int ldc,
-                  double *sdev, std::vector<double> &lam, std::vector<double> &res, hipStream_t s);
+                  double *sdev, std::vector<double> &lam, std::vector<double> &res, int plane_chunk, hipStream_t s);
 
 // ---------------------------------------------------------------- solve state
 // Device buffers one solve keeps across block steps.
@@ -305,7 +305,7 @@ struct SolveBufs {
 // One filtered Lanczos solve advanced block step by block step.
 // One convergence check of T_k (Section 3.2.2) as a self-contained task:
 // a snapshot of T_k and S_k goes in; the Ritz values' candidate set, the
-// residual test and the eigen-decomposition's rotation log come out.  It
+// residual test and the eigen-decomposition's factors come out.  It
 // runs on a host pool thread while the solve keeps stepping.
 struct CheckTask {
     int K = 0, r = 0;

@@ -99,6 +99,10 @@ struct StepShape {
     int win = 0;
     int halo = 0;
 };
+// Y = A X for 1 <= r <= 32 columns.  plane_chunk < 0: walk planes of
+// -plane_chunk rows (StepShape::chunk).
+hipError_t launch_product(int n, const int32_t *rowptr, const int32_t *colind, const double *val, int r,
+                          const double *X, int ldx, double *Y, int ldy, int plane_chunk, hipStream_t s);
 // Host evaluation of the tile-to-XCD traversal the filter kernels use:
 // order[b] = the row tile that block b of a `tiles`-block launch processes
 // (chunk as in StepShape::chunk; rows_per_tile rows per tile).

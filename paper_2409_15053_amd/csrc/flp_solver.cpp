@@ -501,7 +501,7 @@ int solve_finish(Solve &S, flp_result **out) {
         // Ritz vectors of p(A): Y = Q_k W_C
         CK(launch_gemm_nn(n, K, c, 1.0, S.Q, sdev, ldc, 0.0, Y, ldc, s));
         std::vector<double> lam, rres;
-        if (!fp32) CKR(rayleigh_ritz_gen(A, n, c, Y, AY, X, AX, ldc, sdev, lam, rres, s));
+        if (!fp32) CKR(rayleigh_ritz_gen(A, n, c, Y, AY, X, AX, ldc, sdev, lam, rres, S.tile_chunk, s));
         const double alpha = S.alpha, beta = S.beta;
         int cur = c;  // Ritz vectors in the block
         auto worst = [&](int &i0, int &i1) {
@@ -536,8 +536,7 @@ int solve_finish(Solve &S, flp_result **out) {
                 // after the Rayleigh-Ritz that follows it.
                 for (int j0 = 0; j0 < c; j0 += 32) {
                     const int cw = std::min(32, c - j0);
-                    CK(launch_cheb_step<double, double>(n, A->rowptr, A->colind, A->val, cw, Y + j0, ldc, nullptr, 0,
-                                                        nullptr, 0, AY + j0, ldc, 1.0, 0.0, 0.0, 0.0, s));
+                    CK(launch_product(n, A->rowptr, A->colind, A->val, cw, Y + j0, ldc, AY + j0, ldc, S.tile_chunk, s));
                 }
                 const int nch = resid_chunks(n);
                 CK(ensure(w.resid_part, sizeof(double) * (size_t)nch * c));
@@ -555,7 +554,7 @@ int solve_finish(Solve &S, flp_result **out) {
                 S.st.polish_bytes += pbytes;
                 // Rayleigh-Ritz with A on the polished block X; its Ritz
                 // vectors land in Y, then X and Y trade places
-                CKR(rayleigh_ritz_gen(A, n, c, X, AY, Y, AX, ldc, sdev, lam, rres, s));
+                CKR(rayleigh_ritz_gen(A, n, c, X, AY, Y, AX, ldc, sdev, lam, rres, S.tile_chunk, s));
                 std::swap(X, Y);
                 ++S.st.polish_sweeps;
             }
@@ -581,7 +580,7 @@ int solve_finish(Solve &S, flp_result **out) {
                     cur += (int)mixed.size();
                     CKR(orthonormalize_cols(n, cur, Y, X, ldc, sdev, s));
                     CKR(orthonormalize_cols(n, cur, Y, X, ldc, sdev, s));
-                    CKR(rayleigh_ritz(A, n, cur, Y, AY, X, AX, ldc, sdev, lam, rres, s));
+                    CKR(rayleigh_ritz(A, n, cur, Y, AY, X, AX, ldc, sdev, lam, rres, S.tile_chunk, s));
                     ++separations;
                     ++S.st.separations;
                     continue;
@@ -599,7 +598,7 @@ int solve_finish(Solve &S, flp_result **out) {
                 CK(hipStreamSynchronize(s));
                 S.st.t_polish += now() - tp;
                 S.st.polish_bytes += pbytes;
-                CKR(rayleigh_ritz_gen(A, n, c, Y, AY, X, AX, ldc, sdev, lam, rres, s));
+                CKR(rayleigh_ritz_gen(A, n, c, Y, AY, X, AX, ldc, sdev, lam, rres, S.tile_chunk, s));
                 ++S.st.polish_sweeps;
             }
         }
@@ -739,7 +738,7 @@ int solve_warm(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
     CK(launch_transpose_in(n, k, o.warm, Y, ldc, s));
     CK(launch_randn(n, g, Y + k, ldc, o.seed, 0x3A21, s));
     std::vector<double> lam, rres;
-    CKR(rayleigh_ritz_gen(A, n, c0, Y, AY, X, AX, ldc, sdev, lam, rres, s));
+    CKR(rayleigh_ritz_gen(A, n, c0, Y, AY, X, AX, ldc, sdev, lam, rres, 0, s));
     int cur = c0, prev_count = -1, sweeps = 0, separations = 0, i0 = 0, i1 = 0, last_grow = 0, grown = 0;
     auto inside = [&]() {
         i0 = 0;
@@ -765,7 +764,7 @@ int solve_warm(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
             cur += (int)mixed.size();
             CKR(orthonormalize_cols(n, cur, Y, X, ldc, sdev, s));
             CKR(orthonormalize_cols(n, cur, Y, X, ldc, sdev, s));
-            CKR(rayleigh_ritz(A, n, cur, Y, AY, X, AX, ldc, sdev, lam, rres, s));
+            CKR(rayleigh_ritz(A, n, cur, Y, AY, X, AX, ldc, sdev, lam, rres, 0, s));
             ++separations;
             ++st.separations;
             continue;
@@ -800,7 +799,7 @@ int solve_warm(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
             last_grow = sweeps + 1;
             ++grown;
         }
-        CKR(rayleigh_ritz_gen(A, n, cur, Y, AY, X, AX, ldc, sdev, lam, rres, s));
+        CKR(rayleigh_ritz_gen(A, n, cur, Y, AY, X, AX, ldc, sdev, lam, rres, 0, s));
         ++sweeps;
     }
     if (!certified) return kWarmFallback;

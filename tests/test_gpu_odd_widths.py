@@ -53,7 +53,7 @@ def test_overlapping_lanes(torch, r, prec):
     ref = run(0, 0, False, flp.FLP_FORMAT_CSR)
     for fmt in (flp.FLP_FORMAT_CSR, flp.FLP_FORMAT_SELL):
         for lpr in (1, 2, 4, 8, 16):
-            for vec in (2, 4, 8):
+            for vec in (0, 2, 4, 8):
                 for nt in (False, True):
                     assert torch.equal(ref, run(lpr, vec, nt, fmt)), (lpr, vec, nt, fmt)
     got = ref.cpu().numpy()
@@ -63,3 +63,23 @@ def test_overlapping_lanes(torch, r, prec):
     err = np.max(np.abs(got[:, 1:r + 1] - O.filter_apply(A, -g, g, b, V)))
     assert err <= tol, (err, tol)
     flp.flp_release_workspace()
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 257, 4913])
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5, 8, 13, 16, 17, 24, 31, 32])
+def test_product(torch, n, r):
+    """Y = A X for every kind of width on odd leading dimensions: each element
+    rounds at most k products and k sums."""
+    g = np.random.Generator(np.random.PCG64(n * r))
+    A = I.laplacian_3d_13pt(17) if n == 4913 else I.random_sym(n, min(1.0, 6.0 / n), seed=n)
+    X = torch.full((n, r + 3), 7.0, dtype=torch.float64, device="cuda:0")
+    Xh = g.normal(size=(n, r))
+    X[:, 2:r + 2] = torch.from_numpy(Xh).to("cuda:0")
+    Y = torch.full((n, r + 2), -3.0, dtype=torch.float64, device="cuda:0")
+    flp.flp_spmm(flp.DeviceCsr.from_host(A), X[:, 2:r + 2], Y[:, 1:r + 1])
+    got = Y.cpu().numpy()
+    assert (got[:, 0] == -3.0).all() and (got[:, r + 1] == -3.0).all()
+    k = int(np.max(np.diff(A.rowptr)))
+    Aabs = I.Csr(A.n, A.rowptr, A.colind, np.abs(A.val))
+    bound = 2 * (k + 1) * 2.0 ** -53 * O.spmm(Aabs, np.abs(Xh))
+    assert (np.abs(got[:, 1:r + 1] - O.spmm(A, Xh)) <= bound).all()
