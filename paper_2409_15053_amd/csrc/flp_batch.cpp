@@ -252,12 +252,14 @@ int Engine::block_step(double filter_secs) {
         kmax = std::max(kmax, otab_host[i].k);
     }
     const int mt = orth_row_tiles(rows, kmax, c);
+    bool few = true;
     for (int i = 0; i < ns; ++i) {
         Solve &S = *active[i]->S;
         OrthSeg &e = otab_host[i];
         int add[kOrthKinds] = {};
         const int wgs = (int)std::min(1023.0, std::max(16.0, 1024.0 * (double)e.n * e.k / work));
         orth_split(e, c, mt, ns == 1 ? 1023 : wgs, add);
+        few = few && orth_few_partials(e, c);
         for (int t = 0; t < kOrthKinds; ++t) {
             opre_host[(size_t)t * ns + i] = blocks[t];
             blocks[t] += add[t];
@@ -278,7 +280,7 @@ int Engine::block_step(double filter_secs) {
     std::memcpy(ostage + tb, opre_host.data(), pb);
     CK(ensure_grow(otab, tb + pb));
     CK(hipMemcpyAsync(otab.p, ostage, tb + pb, hipMemcpyHostToDevice, s));
-    OrthPlan plan{(const OrthSeg *)otab.p, (const int *)((const char *)otab.p + tb), OrthSeg{}, ns, mt, {}};
+    OrthPlan plan{(const OrthSeg *)otab.p, (const int *)((const char *)otab.p + tb), OrthSeg{}, ns, mt, {}, few};
     for (int t = 0; t < kOrthKinds; ++t) plan.blocks[t] = blocks[t];
     CK(launch_seg_orth(plan, c, s));
     CKR(ensure_pinned((void **)&oout_pin, &oout_pin_bytes, sizeof(double) * slot * ns));

@@ -226,6 +226,7 @@ struct OrthPlan {
     int nseg;
     int mt;  // row tiles of the updates (orth_row_tiles of all the rows)
     int blocks[kOrthKinds];
+    bool sum_in_chol;  // every solve's Gram partials are few (orth_few_partials)
 };
 // Row tiles per wave of W -= Q H for c columns of W against kmax basis
 // columns: 2, 8, or 3 for two tiles with the next group's loads in flight
@@ -234,6 +235,9 @@ int nn_row_tiles(int kmax, int c);
 int orth_row_tiles(int64_t rows, int kmax, int c);
 // whether the projection of c columns on K basis columns runs on FMA
 bool tn_use_fma(int K, int c);
+// Whether the Cholesky block of a split solve sums the partial Gram matrices
+// itself.
+bool orth_few_partials(const OrthSeg &e, int c);
 // Splits the work of one solve over blocks (e.n, e.k, e.kl set; wgs: the
 // blocks its share of a launch should take) and adds its block counts.
 void orth_split(OrthSeg &e, int c, int mt, int wgs, int (&blocks)[kOrthKinds]);

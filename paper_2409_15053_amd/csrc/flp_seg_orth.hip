@@ -279,19 +279,45 @@ __device__ __forceinline__ double lane_value(double x, int from) {
 // down), R2^{-1} and S_j = R2 R1 to out[c^2, 2 c^2).  k = 0: normalisation
 // alone.  The four waves share the column sums of H2; the factorisation is a
 // serial chain that the first wave runs in registers: lane j holds column j
-// of the matrix, padded to 16 x 16 with the identity, and the entries a step
-// needs from other columns come by readlane (5 us at c = 16; the same steps
-// through LDS took 24).
-template <bool ONE>
+// of the matrix, padded to CP x CP with the identity (CP = 1, 4, 8 or 16, the
+// chain's length), and the entries a step needs from other columns come by
+// readlane (c = 1: 2.6 us with the sums, 8.4 padded to 16 without; c = 16: 9.3,
+// the same steps through LDS 24).
+// SUM: the block first adds the nch partial Gram matrices itself, 256 / CP^2
+// threads to an output (instead of an orth_reduce launch, 2.2 us
+// and the gap before it).
+template <bool ONE, int CP, bool SUM>
 __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restrict__ tab, const OrthSeg one, int c,
                                                         int pass) {
     __shared__ double sq[16][16];
+    __shared__ double gs[256];
     const OrthSeg e = ONE ? one : tab[blockIdx.x];
     const int cc = c * c;
     double *out = e.out;
     double *status = out + 2 * cc;
     if (pass == 2 && *status != 0.0) return;  // uniform: every lane reads the same flag
     const bool orth = pass == 1 && e.k > 0;
+    constexpr int NS = 256 / (CP * CP);  // threads per output
+    if constexpr (SUM) {
+        const int o = threadIdx.x / NS, i = o / CP, j = o % CP;
+        const int nch = orth ? e.ublk : e.lblk;
+        double s = 0.0;
+        if (i < c && j < c) {
+            const auto p = as_global(e.part) + i * c + j;
+            int q = threadIdx.x % NS;
+            for (; q + 7 * NS < nch; q += 8 * NS) {
+                double x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = p[(size_t)(q + u * NS) * cc];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += x[u];
+            }
+            for (; q < nch; q += NS) s += p[(size_t)q * cc];
+        }
+#pragma unroll
+        for (int d = 1; d < (NS < WAVE ? NS : WAVE); d *= 2) s += __shfl_xor(s, d, WAVE);
+        gs[threadIdx.x] = s;
+    }
     if (orth) {
         // column sums of squares of H2: thread (ty, tx) takes rows ty, ty + 16, ... of column tx
         const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
@@ -312,12 +338,20 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
     }
     __syncthreads();
     if (threadIdx.x >= WAVE) return;
-    const int lane = threadIdx.x, j = lane % 16;
+    const int lane = threadIdx.x, j = lane % CP;
     const bool col = lane < c;
-    double M[16];
+    double M[CP];
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-        M[i] = (i < c && j < c) ? as_global(e.G)[min(i, c - 1) * c + min(j, c - 1)] : (i == j ? 1.0 : 0.0);
+    for (int i = 0; i < CP; ++i) {
+        double x;
+        if constexpr (SUM) {
+            x = gs[(i * CP + j) * NS];
+            if constexpr (NS > WAVE) x = (gs[0] + gs[WAVE]) + (gs[2 * WAVE] + gs[3 * WAVE]);
+        } else {
+            x = as_global(e.G)[min(i, c - 1) * c + min(j, c - 1)];
+        }
+        M[i] = (i < c && j < c) ? x : (i == j ? 1.0 : 0.0);
+    }
     bool again = false;
     if (orth) {
         const auto h1 = as_global(e.H) + (size_t)(e.k - e.kl - c) * c;
@@ -331,23 +365,23 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
 #pragma unroll
         for (int y = 0; y < 16; ++y) s += sq[y][j];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) g = i == j ? M[i] : g;
+        for (int i = 0; i < CP; ++i) g = i == j ? M[i] : g;
         again = __ballot(col && s > g) != 0ull;
     }
     double thr2 = 1e-300;
     if (pass == 1) {
         double fro2 = 0.0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
+        for (int i = 0; i < CP; ++i)
             if (i < c) fro2 += fmax(lane_value(M[i], i), 0.0);
         const double thr = 1e-7 * sqrt(fro2);
         thr2 = fmax(thr * thr, 1e-300);
     }
     // right-looking Cholesky: M[i] becomes row i of R
     bool bad = false;
-    double inv[16];  // 1 / R[i][i], uniform
+    double inv[CP];  // 1 / R[i][i], uniform
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < CP; ++k) {
         const double d = lane_value(M[k], k);
         const bool ok = k >= c || d > thr2;
         bad = bad || !ok;
@@ -355,7 +389,7 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
         inv[k] = 1.0 / rkk;
         M[k] = j == k ? rkk : (j > k && ok ? M[k] / rkk : 0.0);
 #pragma unroll
-        for (int i = k + 1; i < 16; ++i) {
+        for (int i = k + 1; i < CP; ++i) {
             const double f = lane_value(M[k], i);
             M[i] = fma(-f, M[k], M[i]);
         }
@@ -365,17 +399,17 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
         return;
     }
     // column j of R^{-1} by back substitution
-    double T[16];
+    double T[CP];
 #pragma unroll
-    for (int i = 15; i >= 0; --i) {
+    for (int i = CP - 1; i >= 0; --i) {
         double t = i == j ? 1.0 : 0.0;
 #pragma unroll
-        for (int k = i + 1; k < 16; ++k) t = fma(-lane_value(M[i], k), T[k], t);
+        for (int k = i + 1; k < CP; ++k) t = fma(-lane_value(M[i], k), T[k], t);
         T[i] = t * inv[i];
     }
     double *Ri = pass == 1 ? e.Ri1 : e.Ri2;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
+    for (int i = 0; i < CP; ++i)
         if (i < c && col) {
             if (pass == 1) as_global_mut(e.R1)[i * c + j] = M[i];
             as_global_mut(Ri)[i * c + j] = T[i];
@@ -386,14 +420,14 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
     }
     // S_j = R2 R1 (both upper triangular)
     double *Sj = out + cc;
-    double R1[16];
+    double R1[CP];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) R1[i] = i < c && j < c ? as_global(e.R1)[min(i, c - 1) * c + min(j, c - 1)] : 0.0;
+    for (int i = 0; i < CP; ++i) R1[i] = i < c && j < c ? as_global(e.R1)[min(i, c - 1) * c + min(j, c - 1)] : 0.0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < CP; ++i) {
         double acc = 0.0;
 #pragma unroll
-        for (int k = i; k < 16; ++k) acc = fma(lane_value(M[i], k), R1[k], acc);
+        for (int k = i; k < CP; ++k) acc = fma(lane_value(M[i], k), R1[k], acc);
         if (i < c && col) Sj[i * c + j] = acc;
     }
 }
@@ -528,16 +562,36 @@ __global__ __launch_bounds__(256) void orth_final_kernel(const OrthSeg *__restri
 }
 
 template <bool ONE>
+void launch_chol(const OrthPlan &p, int c, int pass, hipStream_t s) {
+#define FLP_CHOL(CP)                                                                                              \
+    if (c <= CP) {                                                                                                \
+        if (p.sum_in_chol)                                                                                        \
+            hipLaunchKernelGGL((orth_chol_kernel<ONE, CP, true>), dim3(p.nseg), dim3(256), 0, s, p.tab, p.one, c, \
+                               pass);                                                                             \
+        else                                                                                                      \
+            hipLaunchKernelGGL((orth_chol_kernel<ONE, CP, false>), dim3(p.nseg), dim3(256), 0, s, p.tab, p.one,   \
+                               c, pass);                                                                          \
+        return;                                                                                                   \
+    }
+    FLP_CHOL(1)
+    FLP_CHOL(4)
+    FLP_CHOL(8)
+    FLP_CHOL(16)
+#undef FLP_CHOL
+}
+
+#define FLP_ORTH(K, KIND, ...) \
+    hipLaunchKernelGGL(K, dim3(p.blocks[KIND]), dim3(256), 0, s, tab, pre[KIND], ns, p.one, c, ##__VA_ARGS__)
+template <bool ONE>
 void launch_qr(const OrthPlan &p, const int *const *pre, int c, bool have_gram, hipStream_t s) {
     const OrthSeg *tab = p.tab;
     const int ns = p.nseg;
-#define FLP_ORTH(K, KIND, ...)     hipLaunchKernelGGL(K, dim3(p.blocks[KIND]), dim3(256), 0, s, tab, pre[KIND], ns, p.one, c, ##__VA_ARGS__)
     if (!have_gram) FLP_ORTH((orth_gram_kernel<ONE, true>), kOrthLocal);
-    FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, have_gram ? 2 : 3, 0);
-    hipLaunchKernelGGL((orth_chol_kernel<ONE>), dim3(ns), dim3(256), 0, s, tab, p.one, c, 1);
+    if (!p.sum_in_chol) FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, have_gram ? 2 : 3, 0);
+    launch_chol<ONE>(p, c, 1, s);
     FLP_ORTH((orth_gram_kernel<ONE, false>), kOrthLocal);
-    FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, 3, 1);
-    hipLaunchKernelGGL((orth_chol_kernel<ONE>), dim3(ns), dim3(256), 0, s, tab, p.one, c, 2);
+    if (!p.sum_in_chol) FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, 3, 1);
+    launch_chol<ONE>(p, c, 2, s);
     FLP_ORTH((orth_final_kernel<ONE>), kOrthLocal);
 }
 
@@ -577,6 +631,12 @@ int orth_row_tiles(int64_t rows, int kmax, int c) {
     // a few blocks' worth of rows: one tile per wave, so all of them have work
     if (rows < 64 * 512) return 1;
     return nn_row_tiles(kmax, c);
+}
+
+// Few enough partial sums for one block: at most 32 loads per thread, in
+// rounds of 8, about 3 us; one more launch costs as much.
+bool orth_few_partials(const OrthSeg &e, int c) {
+    return (int64_t)std::max(e.lblk, e.k > 0 ? e.ublk : 0) * c * c <= 8192;
 }
 
 void orth_split(OrthSeg &e, int c, int mt, int wgs, int (&blocks)[kOrthKinds]) {
