@@ -914,11 +914,22 @@ int gram_tn(int n, int K, int c, DMat A, const double *B, int64_t ldb, double *d
 // Two passes of classical Gram-Schmidt of W (n x r, ld r) against
 // the first k columns of Q.  H1, H2 (k x r each) stay on the device in hdev[0..2kr).
 int cgs2(DMat Q, int k, int n, double *W, int r, double *hdev, hipStream_t s) {
-    for (int pass = 0; pass < 2; ++pass) {
-        double *H = hdev + (size_t)pass * k * r;
-        CKR(gram_tn(n, k, r, Q, W, r, H, nullptr, s));
-        CK(launch_gemm_nn(n, k, r, -1.0, Q, H, r, 1.0, W, r, s));
+    double *H1 = hdev, *H2 = hdev + (size_t)k * r;
+    CKR(gram_tn(n, k, r, Q, W, r, H1, nullptr, s));
+    if (cgs2_fused_ok(k, r)) {
+        Buf &pb = ws().partials;
+        TnPlan pl{};
+        pl.chunk_rows = cgs2_fused_rows(n, k);
+        pl.nchunks = (n + pl.chunk_rows - 1) / pl.chunk_rows;
+        pl.partial_elems = (size_t)pl.nchunks * k * r;
+        CK(ensure(pb, pl.partial_elems * sizeof(double)));
+        CK(launch_cgs2_fused(n, k, r, Q, H1, W, (double *)pb.p, s));
+        CK(launch_reduce_partials(pl, k, r, (double *)pb.p, H2, r, s, false));
+    } else {
+        CK(launch_gemm_nn(n, k, r, -1.0, Q, H1, r, 1.0, W, r, s));
+        CKR(gram_tn(n, k, r, Q, W, r, H2, nullptr, s));
     }
+    CK(launch_gemm_nn(n, k, r, -1.0, Q, H2, r, 1.0, W, r, s));
     return FLP_OK;
 }
 
