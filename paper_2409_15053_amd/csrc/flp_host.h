@@ -411,8 +411,6 @@ void orth_seg(const Solve &S, OrthSeg &e);
 void orth_account(Solve &S);
 // waits for and applies a check in flight (no-op when there is none)
 int wait_check(Solve &S);
-// all three with a synchronisation (single solve)
-int solve_after_filter(Solve &S);
 // Ritz vectors, Rayleigh-Ritz with A, FP32 polish, result
 int solve_finish(Solve &S, flp_result **out);
 // Device bytes solve_finish allocates for a solve that has converged (its

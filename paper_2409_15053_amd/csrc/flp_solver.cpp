@@ -208,7 +208,6 @@ void orth_account(Solve &S) {
 int step_orth_launch(Solve &S) {
     const int r = S.r;
     CKR(ensure_basis(S, (int64_t)(S.steps + 2) * r));  // the projection's columns and the next block
-    S.t_step0 = now();
     orth_account(S);
     OrthPlan p{};
     p.nseg = 1;
@@ -437,13 +436,6 @@ int step_check(Solve &S, bool async) {
         }
     }
     return FLP_OK;
-}
-
-int solve_after_filter(Solve &S) {
-    CKR(step_orth_launch(S));
-    CK(hipStreamSynchronize(S.s));
-    CKR(step_orth_take(S, S.pin));
-    return step_check(S);
 }
 
 int solve_finish(Solve &S, flp_result **out) {
@@ -917,6 +909,7 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
         }
     } evg{ev};
     while (!S.done) {
+        const double t_it = now();
         CK(hipEventRecord(ev[0], S.s));
         // While a convergence check is still running on the host, the step's
         // launches go out in chunks, each issued after the chunk before the
@@ -964,7 +957,10 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
             }
         }
         CK(hipEventRecord(ev[1], S.s));
-        CK(hipEventSynchronize(ev[1]));
+        // the block step is queued behind the filter that is still running
+        const int rc = stop ? FLP_OK : step_orth_launch(S);
+        CK(hipStreamSynchronize(S.s));
+        CKR(rc);
         float ms = 0;
         CK(hipEventElapsedTime(&ms, ev[0], ev[1]));
         S.st.t_mv += ms * 1e-3;
@@ -975,7 +971,9 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
             S.st.mv += (int64_t)gw * issued;
             break;
         }
-        CKR(solve_after_filter(S));
+        S.t_step0 = std::min(now(), t_it + ms * 1e-3);
+        CKR(step_orth_take(S, S.pin));
+        CKR(step_check(S));
     }
     return solve_finish(S, out);
 }
