@@ -936,9 +936,9 @@ int cgs2(DMat Q, int k, int n, double *W, int r, double *hdev, hipStream_t s) {
 // Block normalisation W = Qn S by Cholesky QR twice (eq. lanczos: S upper
 // triangular, non-negative diagonal).  Columns that are numerically
 // dependent are replaced by random vectors orthogonalised against Q (when
-// given) and the rest of the block; their rows of S are zero.  The Gram
-// matrix carries an absolute rounding error of about u ||W||_F^2, so a
-// Cholesky pivot sqrt(d_i) is only resolved down to ~1e-8 ||W||_F: a column
+// given) and the block's columns before them; their diagonal of S is zero.
+// The Gram matrix carries an absolute rounding error of about u ||W||_F^2, so
+// a Cholesky pivot sqrt(d_i) is only resolved down to ~1e-8 ||W||_F: a column
 // counts as dependent when sqrt(d_i) < 1e-7 ||W||_F.  S: host r x r
 // row-major.
 int block_qr_impl(double *W, int n, int r, const DMat *Q, int k, std::vector<double> &S,

@@ -284,8 +284,8 @@ __device__ __forceinline__ double lane_value(double x, int from) {
 // readlane (c = 1: 2.6 us with the sums, 8.4 padded to 16 without; c = 16: 9.3,
 // the same steps through LDS 24).
 // SUM: the block first adds the nch partial Gram matrices itself, 256 / CP^2
-// threads to an output (instead of an orth_reduce launch, 2.2 us
-// and the gap before it).
+// threads to an output, and writes pass 1's sum to G (instead of an
+// orth_reduce launch, 2.2 us and the gap before it).
 template <bool ONE, int CP, bool SUM>
 __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restrict__ tab, const OrthSeg one, int c,
                                                         int pass) {
@@ -351,6 +351,8 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
             x = as_global(e.G)[min(i, c - 1) * c + min(j, c - 1)];
         }
         M[i] = (i < c && j < c) ? x : (i == j ? 1.0 : 0.0);
+        // the host's repair of dependent columns reads G
+        if (SUM && pass == 1 && i < c && col) as_global_mut(e.G)[i * c + j] = x;
     }
     bool again = false;
     if (orth) {
