@@ -623,30 +623,24 @@ int filter_apply_impl(const flp_filter *p, const flp_csr *A, const double *V, in
     const int n = A->n;
     const bool fp32 = prec == FLP_PREC_FP32_FILTER;
     const size_t es = fp32 ? sizeof(float) : sizeof(double);
-    if (small_filter_fits(p, n, A->nnz, fp32) && !filter_shape_forced()) {
-        const float *a32 = nullptr;
-        if (fp32) CKR(ensure_val32(A, w.val32, &w.val32_src, &w.val32_nnz, &a32, s));
-        const flp_csr *fA = A;
-        bool sell = false;
-        CKR(workspace_storage(A, a32, fp32, format, s, &fA, &a32, &sell));
-        return launch_small_filter(p, fA, a32, sell, r, V, ldv, W, ldw, fp32, s);
-    }
+    const float *v32 = nullptr;
+    if (fp32) CKR(ensure_val32(A, w.val32, &w.val32_src, &w.val32_nnz, &v32, s));
+    const flp_csr *fA = A;
+    const float *fv32 = v32;
+    bool sell = false;
+    CKR(workspace_storage(A, v32, fp32, format, s, &fA, &fv32, &sell));
+    const int small = filter_shape_forced() ? 0 : small_filter_slots(p, A, fA, fp32);
+    if (small > 0) return launch_small_filter(p, small, fA, fv32, sell, r, V, ldv, W, ldw, fp32, s);
     for (auto &u : w.U) CK(ensure(u, es * (size_t)n * r));
     void *U[3] = {w.U[0].p, w.U[1].p, w.U[2].p};
-    const float *v32 = nullptr;
     const void *vfull = V;
     int ldfull = ldv;
     if (fp32) {
-        CKR(ensure_val32(A, w.val32, &w.val32_src, &w.val32_nnz, &v32, s));
         CK(ensure(w.V32, sizeof(float) * (size_t)n * r));
         CK(launch_copy_block(n, r, 1.0, V, ldv, DMat{nullptr, 0, 0, 0}, 0, (float *)w.V32.p, r, s));
         vfull = w.V32.p;
         ldfull = r;
     }
-    const flp_csr *fA = A;
-    const float *fv32 = v32;
-    bool sell = false;
-    CKR(workspace_storage(A, v32, fp32, format, s, &fA, &fv32, &sell));
     FilterTune tn;
     CKR(tune_filter(fA, fv32, r, fp32, true, U, vfull, ldfull, s, &tn, sell));
     const int gw = tn.gw;

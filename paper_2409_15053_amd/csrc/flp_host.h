@@ -188,13 +188,16 @@ int launch_plan_step(const flp_csr *A, const float *val32, int r, const Clenshaw
                      hipStream_t s, StepShape sh = StepShape{}, bool sell = false);
 
 // The whole filter of a small matrix as one launch, one workgroup per column
-// (flp_small.hip): W = p(Ahat) V with the bits of the planned launches.  A
-// (val32: its FP32 values) in CSR or, with sell, as its sliced ELL copy; V
-// and W in FP64 in both precisions.
+// (flp_small.hip): W = p(Ahat) V with the bits of the planned launches.
+// small_filter_slots: the register slots per row with which the matrix A
+// (CSR), read in the form `stored` (A itself or its sliced ELL copy), is
+// filtered so, or 0 where it is not.  launch_small_filter takes that number
+// and the stored form (val32: its FP32 values; sell: a sliced ELL copy); V and
+// W in FP64 in both precisions.
 constexpr int kSmallMaxDegree = 384;  // its coefficients travel as kernel arguments
-bool small_filter_fits(const flp_filter *p, int n, int64_t nnz, bool fp32);
-int launch_small_filter(const flp_filter *p, const flp_csr *A, const float *val32, bool sell, int r, const double *V,
-                        int ldv, double *W, int ldw, bool fp32, hipStream_t s);
+int small_filter_slots(const flp_filter *p, const flp_csr *A, const flp_csr *stored, bool fp32);
+int launch_small_filter(const flp_filter *p, int slots, const flp_csr *A, const float *val32, bool sell, int r,
+                        const double *V, int ldv, double *W, int ldw, bool fp32, hipStream_t s);
 
 // ---------------------------------------------------------------- autotuner
 struct FilterTune {

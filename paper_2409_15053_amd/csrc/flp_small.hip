@@ -203,16 +203,16 @@ hipError_t small_launch(const flp_csr *A, const T *val, bool sell, int r, const 
 }
 
 template <typename T>
-hipError_t small_dispatch(const flp_csr *A, const T *val, bool sell, int r, const double *V, int ldv, double *out,
-                          int ldo, const SmallCoef &co, hipStream_t s) {
+hipError_t small_dispatch(int slots, const flp_csr *A, const T *val, bool sell, int r, const double *V, int ldv,
+                          double *out, int ldo, const SmallCoef &co, hipStream_t s) {
     const int n = A->n;
 #define FLP_SMALL(RPT, W) return small_launch<T, RPT, W>(A, val, sell, r, V, ldv, out, ldo, co, s)
-    if (A->nnz <= 8 * (int64_t)n) {
+    if (slots == 8) {
         if (n <= kThreads) FLP_SMALL(1, 8);
         if (n <= 2 * kThreads) FLP_SMALL(2, 8);
         if (n <= 3 * kThreads) FLP_SMALL(3, 8);
         if (n <= 4 * kThreads) FLP_SMALL(4, 8);
-    } else {
+    } else if (slots == 16) {
         if (n <= kThreads) FLP_SMALL(1, 16);
         if (n <= 2 * kThreads) FLP_SMALL(2, 16);
         if constexpr (sizeof(T) == 4) {
@@ -233,15 +233,25 @@ hipError_t small_dispatch(const flp_csr *A, const T *val, bool sell, int r, cons
 // 196 (degree 6: 19 against 23) and FP32 70 against 199, 1728 rows of 13
 // FP64 70 against 204, 2744 rows of 13 FP32 101 against 200 (degree 5: 27
 // against 23); FP32 at 8000 rows of 7 (spilling) 221 against 200.
-bool small_filter_fits(const flp_filter *p, int n, int64_t nnz, bool fp32) {
-    if (p->m < 4 || p->m > kSmallMaxDegree) return false;
-    if (nnz <= 8 * (int64_t)n) return n <= 4 * kThreads;
-    if (n > 2 * kThreads && p->m < 8) return false;
-    return nnz <= 16 * (int64_t)n && n <= (fp32 ? 3 : 2) * kThreads;
+// The slots are those of the storage that is read (`stored`) where a
+// workgroup has room for 16, so that a sliced ELL copy's padded rows stay in
+// registers; a copy of more than 5/4 of its slots (AUTO's limit) keeps one
+// launch per step, because all the rows of a slice are as long as its longest.
+int small_filter_slots(const flp_filter *p, const flp_csr *A, const flp_csr *stored, bool fp32) {
+    const int n = A->n;
+    if (p->m < 4 || p->m > kSmallMaxDegree) return 0;
+    int slots = 0;
+    if (A->nnz <= 8 * (int64_t)n) {
+        if (n <= 4 * kThreads) slots = stored->nnz > 8 * (int64_t)n && n <= 2 * kThreads ? 16 : 8;
+    } else if (A->nnz <= 16 * (int64_t)n && n <= (fp32 ? 3 : 2) * kThreads) {
+        if (n <= 2 * kThreads || p->m >= 8) slots = 16;
+    }
+    const int64_t rows = ((int64_t)n + kSellC - 1) / kSellC * kSellC;
+    return 4 * stored->nnz <= 5 * slots * rows + 4 * kSellC ? slots : 0;
 }
 
-int launch_small_filter(const flp_filter *p, const flp_csr *A, const float *val32, bool sell, int r, const double *V,
-                        int ldv, double *W, int ldw, bool fp32, hipStream_t s) {
+int launch_small_filter(const flp_filter *p, int slots, const flp_csr *A, const float *val32, bool sell, int r,
+                        const double *V, int ldv, double *W, int ldw, bool fp32, hipStream_t s) {
     // the steps' coefficients are the launch plan's
     const auto plan = clenshaw_plan(p, r, V, ldv, W, ldw, nullptr, nullptr, nullptr, fp32);
     SmallCoef co{};
@@ -256,9 +266,9 @@ int launch_small_filter(const flp_filter *p, const flp_csr *A, const float *val3
     co.beta_last = plan[co.m - 1].beta;
     for (int t = 0; t < co.m; ++t) co.gamma[t] = plan[t].gamma;
     if (fp32)
-        CK(small_dispatch<float>(A, val32, sell, r, V, ldv, W, ldw, co, s));
+        CK(small_dispatch<float>(slots, A, val32, sell, r, V, ldv, W, ldw, co, s));
     else
-        CK(small_dispatch<double>(A, A->val, sell, r, V, ldv, W, ldw, co, s));
+        CK(small_dispatch<double>(slots, A, A->val, sell, r, V, ldv, W, ldw, co, s));
     return FLP_OK;
 }
 

@@ -871,8 +871,8 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
     const flp_csr *fA = S.sell ? &S.SA : A;  // the filter's copy of A
     const float *fv32 = S.sell ? S.sval32 : S.val32;
     // a small matrix is filtered in one launch per block step (nothing to tune or to pace)
-    const bool small = !S.unfiltered && small_filter_fits(S.filt.get(), S.n, A->nnz, fp32) && !filter_shape_forced();
-    if (small) {
+    const int small = S.unfiltered || filter_shape_forced() ? 0 : small_filter_slots(S.filt.get(), A, fA, fp32);
+    if (small > 0) {
         tn.gw = S.r;
     } else {
         CKR(tune_filter(fA, fv32, S.r, fp32, true, U, fp32 ? (const void *)S.V32 : (const void *)S.Vin, S.r, S.s,
@@ -932,8 +932,8 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
             }
             return FLP_OK;
         };
-        if (small) {
-            CKR(launch_small_filter(S.filt.get(), fA, fv32, S.sell, S.r, S.Vin, S.r, S.W, S.r, fp32, S.s));
+        if (small > 0) {
+            CKR(launch_small_filter(S.filt.get(), small, fA, fv32, S.sell, S.r, S.Vin, S.r, S.W, S.r, fp32, S.s));
         } else if (gw == S.r) {
             for (const auto &st : S.plan) {
                 CKR(launch_plan_step(fA, fv32, S.r, st, fp32, S.s, tn.sh, S.sell));
