@@ -155,7 +155,8 @@ int flp_tune_filter(const flp_csr *A, int32_t r, int32_t prec, int32_t format, v
         const flp_csr *fA = A;
         const float *fv32 = v32;
         bool sell = false;
-        CKR(workspace_storage(A, v32, fp32, format, s, &fA, &fv32, &sell));
+        int width = 0;
+        CKR(workspace_storage(A, v32, fp32, format, s, &fA, &fv32, &sell, &width));
         FilterTune tn;
         CKR(tune_filter(fA, fv32, r, fp32, true, U, w.Vg.p, r, s, &tn, sell));
         CK(hipStreamSynchronize(s));

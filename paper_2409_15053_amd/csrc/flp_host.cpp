@@ -500,8 +500,9 @@ int launch_plan_step(const flp_csr *A, const float *val32, int r, const Clenshaw
 }
 
 int build_sell(const flp_csr *A, const float *val32, bool fp32, Buf &boff, Buf &bcol, Buf &bval, flp_csr *out,
-               const float **out32, hipStream_t s, double max_pad, bool *built) {
+               const float **out32, int *width, hipStream_t s, double max_pad, bool *built) {
     *built = false;
+    *width = 0;
     const int n = A->n;
     std::vector<int32_t> rp((size_t)n + 1);
     CK(hipMemcpyAsync(rp.data(), A->rowptr, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToHost, s));
@@ -514,6 +515,7 @@ int build_sell(const flp_csr *A, const float *val32, bool fp32, Buf &boff, Buf &
         for (int j = i * kSellC; j < std::min(n, (i + 1) * kSellC); ++j) w = std::max(w, rp[j + 1] - rp[j]);
         off[i] = (int32_t)tot;
         tot += (int64_t)w * kSellC;
+        *width = std::max(*width, w);
         if (tot > INT32_MAX) return fail(FLP_E_ARG, "the sliced ELL copy of A would exceed 2^31 entries");
     }
     off[nsl] = (int32_t)tot;
@@ -589,11 +591,12 @@ int filter_group_width(int n, int64_t nnz, int r, int prec) {
 // then reused) when format asks for it (FLP_FORMAT_AUTO: only if padding
 // adds under kSellMaxPad).
 int workspace_storage(const flp_csr *A, const float *v32, bool fp32, int format, hipStream_t s,
-                      const flp_csr **fA, const float **fv32, bool *sell) {
+                      const flp_csr **fA, const float **fv32, bool *sell, int *width) {
     Workspace &w = ws();
     *fA = A;
     *fv32 = v32;
     *sell = false;
+    *width = 0;
     if (format == FLP_FORMAT_CSR) return FLP_OK;
     const bool same = w.sell_valid && w.sell_fp32 == fp32 && w.sell_src.n == A->n && w.sell_src.nnz == A->nnz &&
                       w.sell_src.rowptr == A->rowptr && w.sell_src.colind == A->colind &&
@@ -601,8 +604,8 @@ int workspace_storage(const flp_csr *A, const float *v32, bool fp32, int format,
     if (!same) {
         w.sell_valid = false;
         bool built = false;
-        CKR(build_sell(A, v32, fp32, w.sell_off, w.sell_col, w.sell_val, &w.sell_A, &w.sell_val32, s,
-                       format == FLP_FORMAT_SELL ? 1e300 : kSellMaxPad, &built));
+        CKR(build_sell(A, v32, fp32, w.sell_off, w.sell_col, w.sell_val, &w.sell_A, &w.sell_val32,
+                       &w.sell_width, s, format == FLP_FORMAT_SELL ? 1e300 : kSellMaxPad, &built));
         w.sell_src = *A;
         w.sell_src.val32 = v32;
         w.sell_fp32 = fp32;
@@ -611,6 +614,7 @@ int workspace_storage(const flp_csr *A, const float *v32, bool fp32, int format,
     }
     if (w.sell_built) {
         *sell = true;
+        *width = w.sell_width;
         *fA = &w.sell_A;
         *fv32 = w.sell_val32;
     }
@@ -628,8 +632,9 @@ int filter_apply_impl(const flp_filter *p, const flp_csr *A, const double *V, in
     const flp_csr *fA = A;
     const float *fv32 = v32;
     bool sell = false;
-    CKR(workspace_storage(A, v32, fp32, format, s, &fA, &fv32, &sell));
-    const int small = filter_shape_forced() ? 0 : small_filter_slots(p, A, fA, fp32);
+    int width = 0;
+    CKR(workspace_storage(A, v32, fp32, format, s, &fA, &fv32, &sell, &width));
+    const int small = filter_shape_forced() ? 0 : small_filter_slots(p, A, fA, width, fp32);
     if (small > 0) return launch_small_filter(p, small, fA, fv32, sell, r, V, ldv, W, ldw, fp32, s);
     for (auto &u : w.U) CK(ensure(u, es * (size_t)n * r));
     void *U[3] = {w.U[0].p, w.U[1].p, w.U[2].p};

@@ -117,6 +117,7 @@ struct Workspace {
     Buf sell_off, sell_col, sell_val;
     flp_csr sell_src{};
     bool sell_fp32 = false, sell_built = false, sell_valid = false;
+    int sell_width = 0;
     flp_csr sell_A{};
     const float *sell_val32 = nullptr;
     double *pin = nullptr;  // pinned host scratch (pinned_scratch)
@@ -159,11 +160,11 @@ int ensure_val32(const flp_csr *A, Buf &buf, const double **src_cache, int64_t *
 struct SolveBufs;
 // Sliced ELL copy of A into off / col / val (FP64 values, or FP32 ones from val32
 // when fp32): *out describes it (rowptr = slice offsets, nnz = stored
-// entries, val = FP64 values or null), *out32 the FP32 values.  If the copy
-// would store more than max_pad times A's nonzeros nothing is built and
-// *built is false.  Synchronous.
+// entries, val = FP64 values or null), *out32 the FP32 values, *width its
+// widest slice.  If the copy would store more than max_pad times A's nonzeros
+// nothing is built and *built is false.  Synchronous.
 int build_sell(const flp_csr *A, const float *val32, bool fp32, Buf &off, Buf &col, Buf &val, flp_csr *out,
-               const float **out32, hipStream_t s, double max_pad, bool *built);
+               const float **out32, int *width, hipStream_t s, double max_pad, bool *built);
 
 // One launch of the Clenshaw recurrence (Section 2.2):
 // out = alpha (A X) + beta X + gamma V + delta Y on row-major blocks.
@@ -190,12 +191,12 @@ int launch_plan_step(const flp_csr *A, const float *val32, int r, const Clenshaw
 // The whole filter of a small matrix as one launch, one workgroup per column
 // (flp_small.hip): W = p(Ahat) V with the bits of the planned launches.
 // small_filter_slots: the register slots per row with which the matrix A
-// (CSR), read in the form `stored` (A itself or its sliced ELL copy), is
-// filtered so, or 0 where it is not.  launch_small_filter takes that number
+// (CSR), read in the form `stored` (A itself, or its sliced ELL copy with a
+// widest slice of sell_width), is filtered so, or 0 where it is not.  launch_small_filter takes that number
 // and the stored form (val32: its FP32 values; sell: a sliced ELL copy); V and
 // W in FP64 in both precisions.
 constexpr int kSmallMaxDegree = 384;  // its coefficients travel as kernel arguments
-int small_filter_slots(const flp_filter *p, const flp_csr *A, const flp_csr *stored, bool fp32);
+int small_filter_slots(const flp_filter *p, const flp_csr *A, const flp_csr *stored, int sell_width, bool fp32);
 int launch_small_filter(const flp_filter *p, int slots, const flp_csr *A, const float *val32, bool sell, int r,
                         const double *V, int ldv, double *W, int ldw, bool fp32, hipStream_t s);
 
@@ -233,9 +234,10 @@ bool filter_shape_forced();
 int filter_apply_impl(const flp_filter *p, const flp_csr *A, const double *V, int ldv, double *W, int ldw, int r,
                       int prec, hipStream_t s, int format = FLP_FORMAT_CSR);
 // The storage the calling thread's filter products read A in for `format`:
-// *fA = A (and *fv32 = v32), or the workspace's sliced ELL copy of A (*sell).
+// *fA = A (and *fv32 = v32), or the workspace's sliced ELL copy of A (*sell,
+// its widest slice in *width).
 int workspace_storage(const flp_csr *A, const float *v32, bool fp32, int format, hipStream_t s,
-                      const flp_csr **fA, const float **fv32, bool *sell);
+                      const flp_csr **fA, const float **fv32, bool *sell, int *width);
 // Y = p(Ahat) X for c Ritz vectors of A (X, AX = A X, Ritz values lam;
 // n x c blocks with leading dimension ldc) by the residual form: X diag(p(t))
 // in FP64 plus the divided-difference recurrences on the residuals in FP32
@@ -348,6 +350,7 @@ struct Solve {
     bool sell = false;        // the filter reads A's sliced ELL copy SA (values sval32 in FP32)
     flp_csr SA{};
     const float *sval32 = nullptr;
+    int sell_width = 0;       // SA's widest slice
     std::unique_ptr<flp_filter> filt;
     int check_every = 0, max_steps = 0;
     int check_offset = 0;  // checks fall on steps with (steps + check_offset) % check_every == 0

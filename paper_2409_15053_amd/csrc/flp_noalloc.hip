@@ -71,7 +71,7 @@ extern "C" int flp_filter_apply_noalloc(const flp_filter *p, const flp_csr *A, c
     try {
         hipStream_t s = (hipStream_t)stream;
         // a small matrix needs no scratch at all
-        if (const int slots = small_filter_slots(p, A, A, fp32))
+        if (const int slots = small_filter_slots(p, A, A, 0, fp32))
             return launch_small_filter(p, slots, A, A->val32, false, r, V, (int)ldv, W, (int)ldw, fp32, s);
         void *base = nullptr;
         CKR(scratch_ptr(&base));

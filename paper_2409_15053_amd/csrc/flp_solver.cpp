@@ -73,8 +73,8 @@ int solve_setup(Solve &S) {
     if (fp32) CKR(ensure_val32(A, B.val32, &B.val32_src, &B.val32_nnz, &S.val32, s));
     S.sell = false;
     if (o.format != FLP_FORMAT_CSR)
-        CKR(build_sell(A, S.val32, fp32, B.sell_off, B.sell_col, B.sell_val, &S.SA, &S.sval32, s,
-                       o.format == FLP_FORMAT_SELL ? 1e300 : kSellMaxPad, &S.sell));
+        CKR(build_sell(A, S.val32, fp32, B.sell_off, B.sell_col, B.sell_val, &S.SA, &S.sval32,
+                       &S.sell_width, s, o.format == FLP_FORMAT_SELL ? 1e300 : kSellMaxPad, &S.sell));
     S.st.filter_format = S.sell ? FLP_FORMAT_SELL : FLP_FORMAT_CSR;
 
     // PREPROC: spectrum bounds
@@ -871,7 +871,9 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
     const flp_csr *fA = S.sell ? &S.SA : A;  // the filter's copy of A
     const float *fv32 = S.sell ? S.sval32 : S.val32;
     // a small matrix is filtered in one launch per block step (nothing to tune or to pace)
-    const int small = S.unfiltered || filter_shape_forced() ? 0 : small_filter_slots(S.filt.get(), A, fA, fp32);
+    const int small = S.unfiltered || filter_shape_forced()
+                          ? 0
+                          : small_filter_slots(S.filt.get(), A, fA, S.sell_width, fp32);
     if (small > 0) {
         tn.gw = S.r;
     } else {
