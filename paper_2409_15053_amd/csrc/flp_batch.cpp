@@ -241,25 +241,14 @@ int Engine::block_step(double filter_secs) {
     CK(ensure_grow(oout, sizeof(double) * slot * ns));
     // room in each basis for this step's projection and the next block
     for (Job *j : active) CKR(ensure_basis(*j->S, (int64_t)(j->S->steps + 2) * c));
-    // each solve takes blocks by its share of the basis entries
-    double work = 0.0;
-    int64_t rows = 0;
-    int kmax = 0;
-    for (int i = 0; i < ns; ++i) {
-        orth_seg(*active[i]->S, otab_host[i]);
-        work += (double)otab_host[i].n * otab_host[i].k;
-        rows += otab_host[i].n;
-        kmax = std::max(kmax, otab_host[i].k);
-    }
-    const int mt = orth_row_tiles(rows, kmax, c);
-    bool few = true;
+    bool few = false;
     for (int i = 0; i < ns; ++i) {
         Solve &S = *active[i]->S;
         OrthSeg &e = otab_host[i];
         int add[kOrthKinds] = {};
-        const int wgs = (int)std::min(1023.0, std::max(16.0, 1024.0 * (double)e.n * e.k / work));
-        orth_split(e, c, mt, ns == 1 ? 1023 : wgs, add);
-        few = few && orth_few_partials(e, c);
+        orth_seg(S, e);
+        orth_split_shared(e, c, add);
+        few = few || e.few != 0;
         for (int t = 0; t < kOrthKinds; ++t) {
             opre_host[(size_t)t * ns + i] = blocks[t];
             blocks[t] += add[t];
@@ -280,7 +269,12 @@ int Engine::block_step(double filter_secs) {
     std::memcpy(ostage + tb, opre_host.data(), pb);
     CK(ensure_grow(otab, tb + pb));
     CK(hipMemcpyAsync(otab.p, ostage, tb + pb, hipMemcpyHostToDevice, s));
-    OrthPlan plan{(const OrthSeg *)otab.p, (const int *)((const char *)otab.p + tb), OrthSeg{}, ns, mt, {}, few};
+    OrthPlan plan{};
+    plan.tab = (const OrthSeg *)otab.p;
+    plan.pre = (const int *)((const char *)otab.p + tb);
+    plan.nseg = ns;
+    plan.mt = kSharedRowTiles;
+    plan.few = few;
     for (int t = 0; t < kOrthKinds; ++t) plan.blocks[t] = blocks[t];
     CK(launch_seg_orth(plan, c, s));
     CKR(ensure_pinned((void **)&oout_pin, &oout_pin_bytes, sizeof(double) * slot * ns));

@@ -957,8 +957,8 @@ int block_qr_impl(double *W, int n, int r, const DMat *Q, int k, std::vector<dou
     p.one.Ri1 = dev + 2 * rr;
     p.one.Ri2 = dev + 3 * rr;
     p.one.out = dev + 4 * rr;
-    orth_split(p.one, r, 1, 1024, p.blocks);
-    p.sum_in_chol = orth_few_partials(p.one, r);
+    orth_split_single(p.one, r, 1, p.blocks);
+    p.few = p.one.few != 0;
     Workspace &w = ws();
     CK(ensure(w.partials, sizeof(double) * orth_part_elems(p.one, r)));
     p.one.part = (double *)w.partials.p;

@@ -197,7 +197,8 @@ struct OrthSeg {
     int lrows, lblk;      // rows per block and blocks of the passes over W (local projection, Gram, QR)
     int prows, pchunks;   // row chunks of the full projection
     int urows, ublk;      // rows per block and blocks of the updates
-    int fma, pad;         // 1: the full projection runs on FMA (tn_use_fma)
+    int fma;              // 1: the full projection runs on FMA (tn_use_fma)
+    int few;              // 1: the Cholesky block sums the partial Gram matrices itself
     DMat Q;               // basis
     double *W;            // n x c, ld c: the filtered block
     double *H;            // local coefficients ((k - kl) x c), and the full pass's (k x c) at H + k c
@@ -213,9 +214,10 @@ struct OrthSeg {
 // pass is needed).  1 and 3 leave the projected block in W.
 enum { kOrthOk = 0, kOrthDependent = 1, kOrthBreakdown = 2, kOrthAgain = 3 };
 // Launch kinds of a block step: blocks over W, reduction of the local
-// coefficients, updates, full projection on FMA or MFMA, reduction of the
-// full coefficients and of a Gram matrix.
-enum { kOrthLocal = 0, kOrthRedL, kOrthUpd, kOrthFma, kOrthMfma, kOrthRedH, kOrthRedG, kOrthKinds };
+// coefficients, updates with one row tile per wave and with more, full
+// projection on FMA or MFMA, reduction of the full coefficients and of a Gram
+// matrix.
+enum { kOrthLocal = 0, kOrthRedL, kOrthUpd1, kOrthUpd, kOrthFma, kOrthMfma, kOrthRedH, kOrthRedG, kOrthKinds };
 // Launch bookkeeping: the device table with one prefix array of first blocks
 // per kind (nseg each, kind-major), or a single solve passed by value (tab
 // null, nseg 1); each kind's block count.
@@ -224,23 +226,24 @@ struct OrthPlan {
     const int *pre;
     OrthSeg one;
     int nseg;
-    int mt;  // row tiles of the updates (orth_row_tiles of all the rows)
+    int mt;  // row tiles of the kOrthUpd updates (orth_row_tiles)
     int blocks[kOrthKinds];
-    bool sum_in_chol;  // every solve's Gram partials are few (orth_few_partials)
+    bool few;  // some solve has few Gram partials (OrthSeg::few)
 };
 // Row tiles per wave of W -= Q H for c columns of W against kmax basis
 // columns: 2, 8, or 3 for two tiles with the next group's loads in flight
 // (gemm_nn_acc's PIPE); orth_row_tiles: or 1 for a few rows.
 int nn_row_tiles(int kmax, int c);
-int orth_row_tiles(int64_t rows, int kmax, int c);
+int orth_row_tiles(int n, int k, int c);
 // whether the projection of c columns on K basis columns runs on FMA
 bool tn_use_fma(int K, int c);
-// Whether the Cholesky block of a split solve sums the partial Gram matrices
-// itself.
-bool orth_few_partials(const OrthSeg &e, int c);
-// Splits the work of one solve over blocks (e.n, e.k, e.kl set; wgs: the
-// blocks its share of a launch should take) and adds its block counts.
-void orth_split(OrthSeg &e, int c, int mt, int wgs, int (&blocks)[kOrthKinds]);
+// Splits the work of one solve over blocks (e.n, e.k, e.kl set) and adds its
+// block counts: alone on the device, or as one of many.  The split decides the
+// order of the solve's sums and depends on n, k and c alone, so that a
+// solve's bits do not depend on the solves that run beside it.
+void orth_split_single(OrthSeg &e, int c, int mt, int (&blocks)[kOrthKinds]);
+void orth_split_shared(OrthSeg &e, int c, int (&blocks)[kOrthKinds]);
+constexpr int kSharedRowTiles = 2;  // OrthPlan::mt of shared launches
 // first column of the local pass for k basis columns: the last two blocks,
 // from a multiple of 16 (a whole group of the MFMA products)
 inline int orth_local_first(int k, int c) { return (k > 2 * c ? k - 2 * c : 0) & ~15; }

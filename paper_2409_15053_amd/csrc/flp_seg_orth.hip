@@ -283,9 +283,9 @@ __device__ __forceinline__ double lane_value(double x, int from) {
 // chain's length), and the entries a step needs from other columns come by
 // readlane (c = 1: 2.6 us with the sums, 8.4 padded to 16 without; c = 16: 9.3,
 // the same steps through LDS 24).
-// SUM: the block first adds the nch partial Gram matrices itself, 256 / CP^2
-// threads to an output, and writes pass 1's sum to G (instead of an
-// orth_reduce launch, 2.2 us and the gap before it).
+// SUM: a solve of few partial Gram matrices (e.few) has them added by its
+// block first, 256 / CP^2 threads to an output, and pass 1's sum written to G
+// (instead of an orth_reduce launch, 2.2 us and the gap before it).
 template <bool ONE, int CP, bool SUM>
 __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restrict__ tab, const OrthSeg one, int c,
                                                         int pass) {
@@ -298,7 +298,8 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
     if (pass == 2 && *status != 0.0) return;  // uniform: every lane reads the same flag
     const bool orth = pass == 1 && e.k > 0;
     constexpr int NS = 256 / (CP * CP);  // threads per output
-    if constexpr (SUM) {
+    const bool sum = SUM && e.few;         // uniform
+    if (sum) {
         const int o = threadIdx.x / NS, i = o / CP, j = o % CP;
         const int nch = orth ? e.ublk : e.lblk;
         double s = 0.0;
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
 #pragma unroll
     for (int i = 0; i < CP; ++i) {
         double x;
-        if constexpr (SUM) {
+        if (sum) {
             x = gs[(i * CP + j) * NS];
             if constexpr (NS > WAVE) x = (gs[0] + gs[WAVE]) + (gs[2 * WAVE] + gs[3 * WAVE]);
         } else {
@@ -352,7 +353,7 @@ __global__ __launch_bounds__(256) void orth_chol_kernel(const OrthSeg *__restric
         }
         M[i] = (i < c && j < c) ? x : (i == j ? 1.0 : 0.0);
         // the host's repair of dependent columns reads G
-        if (SUM && pass == 1 && i < c && col) as_global_mut(e.G)[i * c + j] = x;
+        if (sum && pass == 1 && i < c && col) as_global_mut(e.G)[i * c + j] = x;
     }
     bool again = false;
     if (orth) {
@@ -567,7 +568,7 @@ template <bool ONE>
 void launch_chol(const OrthPlan &p, int c, int pass, hipStream_t s) {
 #define FLP_CHOL(CP)                                                                                              \
     if (c <= CP) {                                                                                                \
-        if (p.sum_in_chol)                                                                                        \
+        if (p.few)                                                                                                \
             hipLaunchKernelGGL((orth_chol_kernel<ONE, CP, true>), dim3(p.nseg), dim3(256), 0, s, p.tab, p.one, c, \
                                pass);                                                                             \
         else                                                                                                      \
@@ -589,10 +590,11 @@ void launch_qr(const OrthPlan &p, const int *const *pre, int c, bool have_gram, 
     const OrthSeg *tab = p.tab;
     const int ns = p.nseg;
     if (!have_gram) FLP_ORTH((orth_gram_kernel<ONE, true>), kOrthLocal);
-    if (!p.sum_in_chol) FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, have_gram ? 2 : 3, 0);
+    const bool reduce = p.blocks[kOrthRedG] > 0;  // of the solves with many partials
+    if (reduce) FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, have_gram ? 2 : 3, 0);
     launch_chol<ONE>(p, c, 1, s);
     FLP_ORTH((orth_gram_kernel<ONE, false>), kOrthLocal);
-    if (!p.sum_in_chol) FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, 3, 1);
+    if (reduce) FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedG, 3, 1);
     launch_chol<ONE>(p, c, 2, s);
     FLP_ORTH((orth_final_kernel<ONE>), kOrthLocal);
 }
@@ -605,23 +607,22 @@ hipError_t launch_all(const OrthPlan &p, int c, hipStream_t s) {
     for (int t = 0; t < kOrthKinds; ++t) pre[t] = ONE ? nullptr : p.pre + (size_t)t * ns;
     FLP_ORTH((orth_local_kernel<ONE>), kOrthLocal);
     FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedL, 0, 0);
-    if (p.mt == 1)
-        FLP_ORTH((orth_update_kernel<ONE, true, 1, false>), kOrthUpd);
-    else
-        FLP_ORTH((orth_update_kernel<ONE, true, 4, false>), kOrthUpd);
+    if (p.blocks[kOrthUpd1] > 0) FLP_ORTH((orth_update_kernel<ONE, true, 1, false>), kOrthUpd1);
+    if (p.blocks[kOrthUpd] > 0) FLP_ORTH((orth_update_kernel<ONE, true, 4, false>), kOrthUpd);
     if (p.blocks[kOrthFma] > 0)
         hipLaunchKernelGGL((orth_tn_fma_kernel<ONE>), dim3(p.blocks[kOrthFma]), dim3(WAVE), 0, s, tab, pre[kOrthFma],
                            ns, p.one);
     if (p.blocks[kOrthMfma] > 0) FLP_ORTH((orth_tn_mfma_kernel<ONE>), kOrthMfma);
     FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedH, 1, 0);
-    if (p.mt == 8)
-        FLP_ORTH((orth_update_kernel<ONE, false, 8, false>), kOrthUpd);
-    else if (p.mt == 3)
-        FLP_ORTH((orth_update_kernel<ONE, false, 2, true>), kOrthUpd);
-    else if (p.mt == 2)
-        FLP_ORTH((orth_update_kernel<ONE, false, 2, false>), kOrthUpd);
-    else
-        FLP_ORTH((orth_update_kernel<ONE, false, 1, true>), kOrthUpd);
+    if (p.blocks[kOrthUpd1] > 0) FLP_ORTH((orth_update_kernel<ONE, false, 1, true>), kOrthUpd1);
+    if (p.blocks[kOrthUpd] > 0) {
+        if (p.mt == 8)
+            FLP_ORTH((orth_update_kernel<ONE, false, 8, false>), kOrthUpd);
+        else if (p.mt == 3)
+            FLP_ORTH((orth_update_kernel<ONE, false, 2, true>), kOrthUpd);
+        else
+            FLP_ORTH((orth_update_kernel<ONE, false, 2, false>), kOrthUpd);
+    }
     launch_qr<ONE>(p, pre, c, true, s);
     return hipGetLastError();
 #undef FLP_ORTH
@@ -629,42 +630,59 @@ hipError_t launch_all(const OrthPlan &p, int c, hipStream_t s) {
 
 }  // namespace
 
-int orth_row_tiles(int64_t rows, int kmax, int c) {
+int orth_row_tiles(int n, int k, int c) {
     // a few blocks' worth of rows: one tile per wave, so all of them have work
-    if (rows < 64 * 512) return 1;
-    return nn_row_tiles(kmax, c);
+    if (n < 64 * 512) return 1;
+    return nn_row_tiles(k, c);
 }
 
-// Few enough partial sums for one block: at most 32 loads per thread, in
-// rounds of 8, about 3 us; one more launch costs as much.
-bool orth_few_partials(const OrthSeg &e, int c) {
-    return (int64_t)std::max(e.lblk, e.k > 0 ? e.ublk : 0) * c * c <= 8192;
-}
-
-void orth_split(OrthSeg &e, int c, int mt, int wgs, int (&blocks)[kOrthKinds]) {
+namespace {
+// wgs: the blocks that the passes over W should take; cap: most doubles of
+// partial sums.
+void split(OrthSeg &e, int c, int mt, int wgs, size_t cap, int (&blocks)[kOrthKinds]) {
     const auto up = [](int64_t x, int64_t g) { return (int)((x + g - 1) / g * g); };
     const auto cdiv = [](int64_t x, int64_t y) { return (int)((x + y - 1) / y); };
     const int n = e.n;
     e.lrows = std::max(128, up(cdiv(n, wgs), 64));
     e.lblk = cdiv(n, e.lrows);
     blocks[kOrthLocal] += e.lblk;
-    blocks[kOrthRedG] += cdiv(c * c, 16);
-    if (e.k == 0) return;  // normalisation alone
+    // Few enough partial Gram matrices for one block: at most 32 loads per
+    // thread, in rounds of 8, about 3 us; one more launch costs as much.
+    const auto gram = [&](int nb) {
+        e.few = (int64_t)nb * c * c <= 8192;
+        if (!e.few) blocks[kOrthRedG] += cdiv(c * c, 16);
+    };
+    if (e.k == 0) return gram(e.lblk);  // normalisation alone
     const int ug = mt == 1 ? 64 : (mt == 8 ? 512 : 256);
     e.urows = up(cdiv(n, 2 * wgs), ug);
     e.ublk = cdiv(n, e.urows);
-    blocks[kOrthUpd] += e.ublk;
+    blocks[mt == 1 ? kOrthUpd1 : kOrthUpd] += e.ublk;
+    gram(std::max(e.lblk, e.ublk));
     blocks[kOrthRedL] += cdiv((int64_t)(e.k - e.kl) * c, 16);
     e.fma = tn_use_fma(e.k, c);
     const int groups = e.fma ? (e.k + WAVE - 1) / WAVE : (e.k + 127) / 128;
     const int grain = e.fma ? 64 : 128;
-    const size_t cap = wgs >= 1024 ? (size_t)32 << 20 : (size_t)4 << 20;  // doubles of partial sums
     e.prows = std::max(grain, up(cdiv(n, std::max(1, (e.fma ? 4 * wgs : 2 * wgs) / groups)), grain));
     if (!e.fma) e.prows = std::max(e.prows, up(cdiv(n, 512), grain));
     while ((size_t)cdiv(n, e.prows) * e.k * c > cap) e.prows *= 2;
     e.pchunks = cdiv(n, e.prows);
     blocks[e.fma ? kOrthFma : kOrthMfma] += e.pchunks * groups;
     blocks[kOrthRedH] += cdiv((int64_t)e.k * c, 16);
+}
+}  // namespace
+
+void orth_split_single(OrthSeg &e, int c, int mt, int (&blocks)[kOrthKinds]) {
+    split(e, c, mt, 1024, (size_t)32 << 20, blocks);
+}
+
+void orth_split_shared(OrthSeg &e, int c, int (&blocks)[kOrthKinds]) {
+    // 128 rows to a block as long as that is at most 1024 blocks, and one row
+    // tile up to 2^17 rows (ms per batch, one tile / two / by the solve's share
+    // of all active solves' entries: one 30^3 matrix, r = 8, FP64 14.6 / 14.8 /
+    // 14.4; four of 20^3 .. 40^3, r = 4 36.5 / 38.0 / 37.7, with both tiles
+    // among them 39; three of 80^3 .. 100^3, r = 8 604 / 595 / 595)
+    split(e, c, e.n < (1 << 17) ? 1 : kSharedRowTiles, std::min(1024, std::max(16, e.n / 128)), (size_t)4 << 20,
+          blocks);
 }
 
 size_t orth_part_elems(const OrthSeg &e, int c) {

@@ -213,8 +213,8 @@ int step_orth_launch(Solve &S) {
     p.nseg = 1;
     orth_seg(S, p.one);
     p.mt = orth_row_tiles(S.n, p.one.k, r);
-    orth_split(p.one, r, p.mt, 1024, p.blocks);
-    p.sum_in_chol = orth_few_partials(p.one, r);
+    orth_split_single(p.one, r, p.mt, p.blocks);
+    p.few = p.one.few != 0;
     Buf &pb = ws().partials;
     CK(ensure_grow(pb, sizeof(double) * orth_part_elems(p.one, r)));
     p.one.part = (double *)pb.p;
