@@ -140,7 +140,8 @@ typedef struct flp_stats {
                               the deciding convergence check ran on the host */
     int32_t basis_cols;    /* Lanczos basis columns at convergence */
     int32_t polish_sweeps; /* FP64 refinement sweeps (FP32 filter only) */
-    double t_pre;          /* seconds: spectrum bounds (the paper's PREPROC) */
+    double t_pre;          /* seconds: spectrum bounds (the paper's PREPROC); in a batch this solve's
+                              share, by nonzeros and rows, of the run that all its solves share */
     double t_mv;           /* seconds: filter applications (the paper's MV) */
     double t_orth;         /* seconds: reorthogonalisation + block QR (ORTH) */
     double t_check;        /* seconds: convergence checks (host eigensolves) */

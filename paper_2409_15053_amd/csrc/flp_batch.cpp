@@ -464,20 +464,24 @@ int solve_batch_impl(int count, const flp_csr *const *A, const double *alpha, co
         }
         const double tb = now();
         const int rb = estimate_bounds_many(runs, E.s);
+        const double dt = now() - tb;
         if (rb != FLP_OK && rb != FLP_E_NOMEM) return rb;
         ws().W.release();  // the vectors of all matrices at once
+        // each solve's t_pre is its share of the run, by the nonzeros it reads
+        double total = 0.0;
+        for (const BoundsRun &b : runs) total += (double)b.A->nnz + b.A->n;
         for (size_t i = 0; rb == FLP_OK && i < runs.size(); ++i) {
             if (runs[i].code != FLP_OK) continue;  // its own set-up reports it
             of[i]->lmin = runs[i].lmin;
             of[i]->lmax = runs[i].lmax;
-            of[i]->st.t_pre = now() - tb;
+            of[i]->st.t_pre = dt * ((double)runs[i].A->nnz + runs[i].A->n) / total;
             of[i]->have_bounds = true;
         }
     }
-    // Set-up (filter, buffers, start block) is a chain of
-    // small launches and host round trips per solve: the solves' set-ups run
-    // on a few threads at once, each with a stream of its own (the threads'
-    // workspaces are released when they join), and join the engine in order.
+    // Set-up (filter, buffers, start block) is a chain of small launches and
+    // host round trips per solve: the solves' set-ups run on a few threads at
+    // once, each with a stream of its own (the threads' workspaces are released
+    // when they join), and join the engine in order.
     {
         const int nt = std::max(1, std::min(count, kSetupThreads));
         const int dev = E.device;
