@@ -154,7 +154,9 @@ typedef struct flp_stats {
     int32_t filter_format; /* storage the filter read A in: FLP_FORMAT_CSR or FLP_FORMAT_SELL */
     int32_t filter_group_width;     /* filter launch configuration of a single solve (0 in
                                        batched and serving results): columns per launch, */
-    int32_t filter_lanes_per_row;   /* lanes per matrix row, */
+    int32_t filter_lanes_per_row;   /* lanes per matrix row (0, and 0 in the rest of the
+                                       configuration: the whole filter of a small matrix in one
+                                       launch, which has no step's shape), */
     int32_t filter_cols_per_lane;   /* columns per lane and */
     int32_t filter_streaming_loads; /* nontemporal loads of V and U_{k+2} (1) or not (0) and */
     int32_t filter_tile_chunk;      /* the tile-to-XCD mapping (flp_tune_info.tile_chunk) */

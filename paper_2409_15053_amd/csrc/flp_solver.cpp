@@ -882,7 +882,8 @@ int solve_cold(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
     }
     const int gw = tn.gw;
     {
-        const StepShape used = step_shape_ok(gw, fp32, tn.sh) ? tn.sh : default_step_shape(gw, fp32);
+        const StepShape used =
+            small > 0 ? StepShape{0, 0} : (step_shape_ok(gw, fp32, tn.sh) ? tn.sh : default_step_shape(gw, fp32));
         S.st.filter_group_width = gw;
         S.st.filter_lanes_per_row = used.lpr;
         S.st.filter_cols_per_lane = used.vec;
