@@ -273,7 +273,7 @@ int Engine::block_step(double filter_secs) {
     plan.tab = (const OrthSeg *)otab.p;
     plan.pre = (const int *)((const char *)otab.p + tb);
     plan.nseg = ns;
-    plan.mt = kSharedRowTiles;
+    plan.upd = kSharedRowTiles;
     plan.few = few;
     for (int t = 0; t < kOrthKinds; ++t) plan.blocks[t] = blocks[t];
     CK(launch_seg_orth(plan, c, s));

@@ -957,7 +957,7 @@ int block_qr_impl(double *W, int n, int r, const DMat *Q, int k, std::vector<dou
     p.one.Ri1 = dev + 2 * rr;
     p.one.Ri2 = dev + 3 * rr;
     p.one.out = dev + 4 * rr;
-    orth_split_single(p.one, r, 1, p.blocks);
+    orth_split_single(p.one, r, RowTiles{1, false}, p.blocks);  // (no updates)
     p.few = p.one.few != 0;
     Workspace &w = ws();
     CK(ensure(w.partials, sizeof(double) * orth_part_elems(p.one, r)));

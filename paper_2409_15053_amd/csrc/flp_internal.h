@@ -218,6 +218,12 @@ enum { kOrthOk = 0, kOrthDependent = 1, kOrthBreakdown = 2, kOrthAgain = 3 };
 // projection on FMA or MFMA, reduction of the full coefficients and of a Gram
 // matrix.
 enum { kOrthLocal = 0, kOrthRedL, kOrthUpd1, kOrthUpd, kOrthFma, kOrthMfma, kOrthRedH, kOrthRedG, kOrthKinds };
+// Row tiles of 16 rows per wave of an update, and whether the next group's
+// loads are in flight meanwhile (gemm_nn_acc's PIPE).
+struct RowTiles {
+    int tiles;
+    bool ahead;
+};
 // Launch bookkeeping: the device table with one prefix array of first blocks
 // per kind (nseg each, kind-major), or a single solve passed by value (tab
 // null, nseg 1); each kind's block count.
@@ -226,24 +232,23 @@ struct OrthPlan {
     const int *pre;
     OrthSeg one;
     int nseg;
-    int mt;  // row tiles of the kOrthUpd updates (orth_row_tiles)
+    RowTiles upd;  // of the kOrthUpd updates (orth_row_tiles)
     int blocks[kOrthKinds];
     bool few;  // some solve has few Gram partials (OrthSeg::few)
 };
-// Row tiles per wave of W -= Q H for c columns of W against kmax basis
-// columns: 2, 8, or 3 for two tiles with the next group's loads in flight
-// (gemm_nn_acc's PIPE); orth_row_tiles: or 1 for a few rows.
-int nn_row_tiles(int kmax, int c);
-int orth_row_tiles(int n, int k, int c);
+// W -= Q H for c columns of W against k basis columns; orth_row_tiles: one
+// tile for a few rows.
+RowTiles nn_row_tiles(int k, int c);
+RowTiles orth_row_tiles(int n, int k, int c);
 // whether the projection of c columns on K basis columns runs on FMA
 bool tn_use_fma(int K, int c);
 // Splits the work of one solve over blocks (e.n, e.k, e.kl set) and adds its
 // block counts: alone on the device, or as one of many.  The split decides the
 // order of the solve's sums and depends on n, k and c alone, so that a
 // solve's bits do not depend on the solves that run beside it.
-void orth_split_single(OrthSeg &e, int c, int mt, int (&blocks)[kOrthKinds]);
+void orth_split_single(OrthSeg &e, int c, RowTiles upd, int (&blocks)[kOrthKinds]);
 void orth_split_shared(OrthSeg &e, int c, int (&blocks)[kOrthKinds]);
-constexpr int kSharedRowTiles = 2;  // OrthPlan::mt of shared launches
+constexpr RowTiles kSharedRowTiles{2, false};  // OrthPlan::upd of shared launches
 // first column of the local pass for k basis columns: the last two blocks,
 // from a multiple of 16 (a whole group of the MFMA products)
 inline int orth_local_first(int k, int c) { return (k > 2 * c ? k - 2 * c : 0) & ~15; }

@@ -190,9 +190,9 @@ hipError_t launch_reduce_partials(const TnPlan &pl, int K, int c, const double *
 // K = 320 - / 546 / 578, K = 640 - / 1010 / 1031; 16 columns, K = 160 302 /
 // 309 / -, K = 320 - / 591 / 601, K = 720 - / 1185 / 1157; n = 27000, 8
 // columns, K = 300: 19 / 16 / -.
-int nn_row_tiles(int kmax, int c) {
-    if (kmax < 256) return 2;
-    return c <= 8 ? 3 : (kmax >= 320 ? 8 : 2);
+RowTiles nn_row_tiles(int k, int c) {
+    if (k >= 256 && c <= 8) return {2, true};
+    return {k >= 320 ? 8 : 2, false};
 }
 
 hipError_t launch_gemm_nn(int n, int K, int c, double alpha, DMat A, const double *B, int64_t ldb, double beta,
@@ -208,10 +208,10 @@ hipError_t launch_gemm_nn(int n, int K, int c, double alpha, DMat A, const doubl
     if (c > 16) {
         go(gemm_nn_kernel<2, 4, false>, 2, 4);
     } else {
-        const int mt = nn_row_tiles(K, c);
-        if (mt == 8)
+        const RowTiles t = nn_row_tiles(K, c);
+        if (t.tiles == 8)
             go(gemm_nn_kernel<8, 1, false>, 8, 1);
-        else if (mt == 3)
+        else if (t.ahead)
             go(gemm_nn_kernel<2, 1, true>, 2, 1);
         else
             go(gemm_nn_kernel<2, 1, false>, 2, 1);

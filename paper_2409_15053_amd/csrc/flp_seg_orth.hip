@@ -616,9 +616,9 @@ hipError_t launch_all(const OrthPlan &p, int c, hipStream_t s) {
     FLP_ORTH((orth_reduce_kernel<ONE>), kOrthRedH, 1, 0);
     if (p.blocks[kOrthUpd1] > 0) FLP_ORTH((orth_update_kernel<ONE, false, 1, true>), kOrthUpd1);
     if (p.blocks[kOrthUpd] > 0) {
-        if (p.mt == 8)
+        if (p.upd.tiles == 8)
             FLP_ORTH((orth_update_kernel<ONE, false, 8, false>), kOrthUpd);
-        else if (p.mt == 3)
+        else if (p.upd.ahead)
             FLP_ORTH((orth_update_kernel<ONE, false, 2, true>), kOrthUpd);
         else
             FLP_ORTH((orth_update_kernel<ONE, false, 2, false>), kOrthUpd);
@@ -630,16 +630,16 @@ hipError_t launch_all(const OrthPlan &p, int c, hipStream_t s) {
 
 }  // namespace
 
-int orth_row_tiles(int n, int k, int c) {
+RowTiles orth_row_tiles(int n, int k, int c) {
     // a few blocks' worth of rows: one tile per wave, so all of them have work
-    if (n < 64 * 512) return 1;
+    if (n < 64 * 512) return {1, true};
     return nn_row_tiles(k, c);
 }
 
 namespace {
 // wgs: the blocks that the passes over W should take; cap: most doubles of
 // partial sums.
-void split(OrthSeg &e, int c, int mt, int wgs, size_t cap, int (&blocks)[kOrthKinds]) {
+void split(OrthSeg &e, int c, RowTiles upd, int wgs, size_t cap, int (&blocks)[kOrthKinds]) {
     const auto up = [](int64_t x, int64_t g) { return (int)((x + g - 1) / g * g); };
     const auto cdiv = [](int64_t x, int64_t y) { return (int)((x + y - 1) / y); };
     const int n = e.n;
@@ -653,10 +653,11 @@ void split(OrthSeg &e, int c, int mt, int wgs, size_t cap, int (&blocks)[kOrthKi
         if (!e.few) blocks[kOrthRedG] += cdiv(c * c, 16);
     };
     if (e.k == 0) return gram(e.lblk);  // normalisation alone
-    const int ug = mt == 1 ? 64 : (mt == 8 ? 512 : 256);
+    // rows that a block's 4 waves update at once (the local pass takes four tiles for two)
+    const int ug = upd.tiles == 1 ? 64 : (upd.tiles == 8 ? 512 : 256);
     e.urows = up(cdiv(n, 2 * wgs), ug);
     e.ublk = cdiv(n, e.urows);
-    blocks[mt == 1 ? kOrthUpd1 : kOrthUpd] += e.ublk;
+    blocks[upd.tiles == 1 ? kOrthUpd1 : kOrthUpd] += e.ublk;
     gram(std::max(e.lblk, e.ublk));
     blocks[kOrthRedL] += cdiv((int64_t)(e.k - e.kl) * c, 16);
     e.fma = tn_use_fma(e.k, c);
@@ -671,8 +672,8 @@ void split(OrthSeg &e, int c, int mt, int wgs, size_t cap, int (&blocks)[kOrthKi
 }
 }  // namespace
 
-void orth_split_single(OrthSeg &e, int c, int mt, int (&blocks)[kOrthKinds]) {
-    split(e, c, mt, 1024, (size_t)32 << 20, blocks);
+void orth_split_single(OrthSeg &e, int c, RowTiles upd, int (&blocks)[kOrthKinds]) {
+    split(e, c, upd, 1024, (size_t)32 << 20, blocks);
 }
 
 void orth_split_shared(OrthSeg &e, int c, int (&blocks)[kOrthKinds]) {
@@ -681,8 +682,8 @@ void orth_split_shared(OrthSeg &e, int c, int (&blocks)[kOrthKinds]) {
     // of all active solves' entries: one 30^3 matrix, r = 8, FP64 14.6 / 14.8 /
     // 14.4; four of 20^3 .. 40^3, r = 4 36.5 / 38.0 / 37.7, with both tiles
     // among them 39; three of 80^3 .. 100^3, r = 8 604 / 595 / 595)
-    split(e, c, e.n < (1 << 17) ? 1 : kSharedRowTiles, std::min(1024, std::max(16, e.n / 128)), (size_t)4 << 20,
-          blocks);
+    split(e, c, e.n < (1 << 17) ? RowTiles{1, true} : kSharedRowTiles, std::min(1024, std::max(16, e.n / 128)),
+          (size_t)4 << 20, blocks);
 }
 
 size_t orth_part_elems(const OrthSeg &e, int c) {

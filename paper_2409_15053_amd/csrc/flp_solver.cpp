@@ -212,8 +212,8 @@ int step_orth_launch(Solve &S) {
     OrthPlan p{};
     p.nseg = 1;
     orth_seg(S, p.one);
-    p.mt = orth_row_tiles(S.n, p.one.k, r);
-    orth_split_single(p.one, r, p.mt, p.blocks);
+    p.upd = orth_row_tiles(S.n, p.one.k, r);
+    orth_split_single(p.one, r, p.upd, p.blocks);
     p.few = p.one.few != 0;
     Buf &pb = ws().partials;
     CK(ensure_grow(pb, sizeof(double) * orth_part_elems(p.one, r)));
