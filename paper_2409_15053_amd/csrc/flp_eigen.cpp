@@ -183,6 +183,61 @@ void band_base(Band &M, EigLog &log, double *Zt, int nrp) {
     band_body<NV>(M, log, Zt, nrp);
 }
 
+// Half-width 2 (a block of 2 vectors): the same steps on single entries, where
+// half of every vector of four would be padding.
+inline __attribute__((always_inline)) void band2_body(Band &M, EigLog &log, double *Zt, int nrp) {
+#pragma clang fp contract(off)
+    const int N = M.N, ld = M.ld;
+    double *B = M.B.data();
+    for (int j = 0; j + 2 < N; ++j) {
+        for (int c = j, i0 = j + 1; i0 + 1 < N; c = i0, i0 += 2) {
+            double *x = B + (size_t)c * ld + (i0 - c);
+            const double x0 = x[0], x1 = x[1];
+            const double sigma = x1 * x1;
+            x[1] = 0.0;
+            if (sigma < 1e-280) continue;
+            const double mu = -std::copysign(std::sqrt(x0 * x0 + sigma), x0);
+            const double v0 = x0 - mu;
+            const double bt = -v0 / mu, v1 = x1 / v0;
+            x[0] = mu;
+            log.row.push_back(i0);
+            log.beta.push_back(bt);
+            log.v.push_back(1.0);
+            log.v.push_back(v1);
+            if (i0 - c == 2) {
+                double *a = x + ld - 1;  // column c + 1
+                const double f = bt * (a[0] + v1 * a[1]);
+                a[0] -= f;
+                a[1] -= f * v1;
+            }
+            double *p = B + (size_t)i0 * ld, *q = p + ld;
+            const double p0 = bt * (p[0] + v1 * p[1]), p1 = bt * (p[1] + v1 * q[0]);
+            const double K = 0.5 * bt * (p0 + v1 * p1);
+            const double w0 = p0 - K, w1 = p1 - K * v1;
+            p[0] -= 2.0 * w0;
+            p[1] -= w0 * v1 + w1;
+            q[0] -= 2.0 * (w1 * v1);
+            for (int i = 0; i < 2; ++i) {  // the two rows below
+                const double t = bt * (p[2 + i] + v1 * q[1 + i]);
+                p[2 + i] -= t;
+                q[1 + i] -= v1 * t;
+            }
+            double *z = Zt + (size_t)i0 * nrp;
+            for (int i = 0; i < nrp; i += 4) {
+                const v4 a = ld4(z + i), b = ld4(z + nrp + i);
+                const v4 y = bt * (a + v1 * b);
+                st4(z + i, a - y);
+                st4(z + nrp + i, b - v1 * y);
+            }
+        }
+    }
+}
+__attribute__((target("avx2"))) void band2_avx2(Band &M, EigLog &log, double *Zt, int nrp) {
+    if (nrp == 4) return band2_body(M, log, Zt, 4);
+    band2_body(M, log, Zt, nrp);
+}
+void band2_base(Band &M, EigLog &log, double *Zt, int nrp) { band2_body(M, log, Zt, nrp); }
+
 // Widest band that is reduced as one; without tracked rows a wider one goes
 // through the dense reduction.
 constexpr int kMaxBand = 128;
@@ -202,7 +257,7 @@ void band_to_tridiag(Band &M, EigLog &log, double *Zt, int nrp) {
 #define FLP_BAND(NV) (cpu_avx2() ? &band_avx2<NV> : &band_base<NV>)
     Fn fn = FLP_BAND(32);
     switch (band_vecs(M.b)) {
-        case 1: fn = FLP_BAND(1); break;
+        case 1: fn = M.b == 2 ? (cpu_avx2() ? &band2_avx2 : &band2_base) : FLP_BAND(1); break;
         case 2: fn = FLP_BAND(2); break;
         case 4: fn = FLP_BAND(4); break;
         case 8: fn = FLP_BAND(8); break;
@@ -401,6 +456,16 @@ inline __attribute__((always_inline)) void vectors_tile(const EigLog &log, const
         const int i0 = log.row[i], L = std::min(log.b, N - i0);
         const double *v = log.v.data() + i * log.b;
         double *z = tile + (size_t)i0 * W;
+        if (L == 2) {
+            const double v1 = v[1], bt = log.beta[i];
+            for (int q = 0; q < NW; ++q) {
+                const v4 a = ld4(z + 4 * q), c = ld4(z + W + 4 * q);
+                const v4 t = bt * (a + v1 * c);
+                st4(z + 4 * q, a - t);
+                st4(z + W + 4 * q, c - v1 * t);
+            }
+            continue;
+        }
         v4 y[NW];
         for (int q = 0; q < NW; ++q) y[q] = v4(0.0);
         for (int u = 0; u < L; ++u)
