@@ -915,7 +915,7 @@ int gram_tn(int n, int K, int c, DMat A, const double *B, int64_t ldb, double *d
 int cgs2(DMat Q, int k, int n, double *W, int r, double *hdev, hipStream_t s) {
     double *H1 = hdev, *H2 = hdev + (size_t)k * r;
     CKR(gram_tn(n, k, r, Q, W, r, H1, nullptr, s));
-    if (cgs2_fused_ok(k, r)) {
+    if (cgs2_fused_ok(n, k, r)) {
         Buf &pb = ws().partials;
         TnPlan pl{};
         pl.chunk_rows = cgs2_fused_rows(n, k);

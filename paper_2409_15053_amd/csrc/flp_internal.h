@@ -269,7 +269,7 @@ struct TnPlan {
 TnPlan plan_tn(int n, int K, int c);
 // W -= Q H (n x c, ld c) with the partial sums of Q^T W after it, one per
 // block of cgs2_fused_rows(n, K) rows (K x c each), in one read of Q.
-bool cgs2_fused_ok(int K, int c);
+bool cgs2_fused_ok(int n, int K, int c);
 int cgs2_fused_rows(int n, int K);
 hipError_t launch_cgs2_fused(int n, int K, int c, DMat Q, const double *H, double *W, double *part, hipStream_t s);
 // sym (K == c and A^T B symmetric, as B = A or B = M A with M symmetric):
