@@ -160,8 +160,9 @@ int cgs2_fused_rows(int n, int K) {
 // loop's barrier is what they wait for (whole calls, us, two kernels / one: n =
 // 1e6, c = 1, K = 8 171 / 226, K = 32 214 / 260; c = 8, K = 8 180 / 231, K = 32
 // 280 / 290; c = 16, K = 20 277 / 298; n = 2e5, c = 8, K = 8 74 / 86, K = 32
-// 87 / 92.  Wider: c = 1, K = 36 305 / 294; c = 8, K = 40 380 / 340; c = 16, K =
-// 24 329 / 317.  Fewer rows: n = 1e5, c = 8, K = 8 69 / 70, K = 32 75 / 71).
+// 87 / 92; the other side of the line, with the partial sums' reduction of the
+// time: n = 1e6, c = 1, K = 36 305 / 294, c = 8, K = 40 380 / 340, c = 16, K =
+// 24 329 / 317; n = 1e5, c = 8, K = 8 69 / 70).
 bool cgs2_fused_ok(int n, int K, int c) {
     if (c > 16 || K > 640) return false;
     return n <= (1 << 17) || K > (c <= 8 ? 32 : 20);
