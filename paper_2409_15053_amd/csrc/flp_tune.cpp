@@ -280,8 +280,14 @@ int tune_filter(const flp_csr *A, const float *val32, int r, bool fp32, bool all
     int tried = 0;
     for (int gw = r; gw >= 1; gw /= 2) {
         if (r % gw != 0 || (gw != r && !allow_groups)) continue;
-        std::vector<StepShape> cands;
-        for (StepShape sh : step_shape_candidates(gw, fp32, true)) {
+        std::vector<StepShape> shapes = step_shape_candidates(gw, fp32, true), cands;
+        // Three columns in FP32 have pieces of 8 bytes only, two overlapping
+        // lanes: faster than a lane per column where a row has few nonzeros,
+        // slower where it has many (us for 25 steps, lanes / pieces: 5 points,
+        // 950^2 619 / 555; 7 points, 110^3 855 / 755; 13 points, 80^3 564 / 630,
+        // 110^3 1170 / 1375), so both are timed.
+        if (fp32 && gw == 3) shapes.push_back(default_step_shape(gw, fp32));
+        for (StepShape sh : shapes) {
             for (int ch : kTileChunks) {
                 sh.chunk = ch;
                 cands.push_back(sh);
