@@ -1131,21 +1131,31 @@ int estimate_bounds_impl(const flp_csr *A, int k0, uint64_t seed, double *lmin, 
 // ------------------------------------------------------------------ solve
 
 // Y (n x c, ld ldc) <- Y R^{-1} with Y^T Y = R^T R (one Cholesky QR pass);
-// tmp is an n x c work block.
-int orthonormalize_cols(int n, int c, double *&Y, double *&tmp, int ldc, double *sdev, hipStream_t s) {
+// tmp is an n x c work block.  A column that depends on those before it to
+// rounding (its pivot is no longer positive) adds nothing to the span and is
+// left out: c is then smaller on return, the others keep their order.  The
+// first `lead` columns have to stay.
+int orthonormalize_cols(int n, int &c, int lead, double *&Y, double *&tmp, int ldc, double *sdev, hipStream_t s) {
     std::vector<double> G((size_t)c * c), R, Ri;
     std::vector<int> bad;
     CKR(gram_tn(n, c, c, plain_mat(Y, ldc), Y, ldc, sdev, G.data(), s, true));
     cholesky_flag(c, G.data(), 1e-300, R, bad);
-    for (int i = 0; i < c; ++i)
-        if (bad[i]) return fail(FLP_E_DEVICE, "Ritz block lost rank");
-    upper_inverse(c, R, Ri);
+    std::vector<int> good;
+    for (int i = 0; i < c; ++i) {
+        if (!bad[i])
+            good.push_back(i);
+        else if (i < lead || !std::isfinite(G[(size_t)i * c + i]))
+            return fail(FLP_E_DEVICE, "Ritz block lost rank");
+    }
+    upper_inverse(c, R, Ri);  // (a left-out column's row is zero beyond its diagonal)
+    const int m = (int)good.size();
     std::vector<double> Rp((size_t)c * ldc, 0.0);
     for (int i = 0; i < c; ++i)
-        for (int j = 0; j < c; ++j) Rp[(size_t)i * ldc + j] = Ri[(size_t)i * c + j];
+        for (int j = 0; j < m; ++j) Rp[(size_t)i * ldc + j] = Ri[(size_t)i * c + good[j]];
     CK(h2d(sdev, Rp.data(), sizeof(double) * Rp.size(), s));
-    CK(launch_gemm_nn(n, c, c, 1.0, plain_mat(Y, ldc), sdev, ldc, 0.0, tmp, ldc, s));
+    CK(launch_gemm_nn(n, c, m, 1.0, plain_mat(Y, ldc), sdev, ldc, 0.0, tmp, ldc, s));
     std::swap(Y, tmp);
+    c = m;
     return FLP_OK;
 }
 

@@ -283,7 +283,7 @@ struct BoundsRun {
     int code = FLP_OK;          // out
 };
 int estimate_bounds_many(std::vector<BoundsRun> &runs, hipStream_t s);
-int orthonormalize_cols(int n, int c, double *&Y, double *&tmp, int ldc, double *sdev, hipStream_t s);
+int orthonormalize_cols(int n, int &c, int lead, double *&Y, double *&tmp, int ldc, double *sdev, hipStream_t s);
 // The same for a block Y whose columns need not be orthonormal (Y itself is
 // left as it is): replaces orthonormalising Y and then rayleigh_ritz.
 int rayleigh_ritz_gen(const flp_csr *A, int n, int c, const double *Y, double *AY, double *X, double *AX, int ldc,

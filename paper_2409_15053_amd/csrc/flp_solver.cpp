@@ -570,9 +570,10 @@ int solve_finish(Solve &S, flp_result **out) {
                     for (size_t t = 0; t < mixed.size(); ++t)
                         CK(launch_copy_block(n, 1, 1.0, AX + mixed[t], ldc, plain_mat(Y, ldc), cur + (int)t, nullptr,
                                              0, s));
+                    const int before = cur;  // the new columns depend on each other at times
                     cur += (int)mixed.size();
-                    CKR(orthonormalize_cols(n, cur, Y, X, ldc, sdev, s));
-                    CKR(orthonormalize_cols(n, cur, Y, X, ldc, sdev, s));
+                    CKR(orthonormalize_cols(n, cur, before, Y, X, ldc, sdev, s));
+                    CKR(orthonormalize_cols(n, cur, before, Y, X, ldc, sdev, s));
                     CKR(rayleigh_ritz(A, n, cur, Y, AY, X, AX, ldc, sdev, lam, rres, S.tile_chunk, s));
                     ++separations;
                     ++S.st.separations;
@@ -754,9 +755,10 @@ int solve_warm(const flp_csr *A, double alpha, double beta, const flp_opts &o, f
             CK(launch_copy_block(n, cur, 1.0, X, ldc, plain_mat(Y, ldc), 0, nullptr, 0, s));
             for (size_t t = 0; t < mixed.size(); ++t)
                 CK(launch_copy_block(n, 1, 1.0, AX + mixed[t], ldc, plain_mat(Y, ldc), cur + (int)t, nullptr, 0, s));
+            const int before = cur;  // the new columns depend on each other at times
             cur += (int)mixed.size();
-            CKR(orthonormalize_cols(n, cur, Y, X, ldc, sdev, s));
-            CKR(orthonormalize_cols(n, cur, Y, X, ldc, sdev, s));
+            CKR(orthonormalize_cols(n, cur, before, Y, X, ldc, sdev, s));
+            CKR(orthonormalize_cols(n, cur, before, Y, X, ldc, sdev, s));
             CKR(rayleigh_ritz(A, n, cur, Y, AY, X, AX, ldc, sdev, lam, rres, 0, s));
             ++separations;
             ++st.separations;
